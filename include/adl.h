@@ -151,29 +151,27 @@ int adl_op_profile_read_kind(const adl_op* op, int kind, double* kernel_ms, long
 int adl_op_set_tiling(adl_op* op, int rows, int cols_per_lane);
 
 /* Newton terms per launch of a sweep (Sec. 2 recurrence): mode = 1 (the
- * default) computes four terms per launch on grids below 2^20 points
- * (mode 4's form, y_{k+1} .. y_{k+3} kept on chip) and, from 2^20 points
- * on, three (mode 5's form: read y_k, the fields and p_k once, write y_{k+3}
- * and p_{k+3}; with FP64 Newton vectors and no augmented column among terms
- * 1 .. 3 the first launch takes three terms too, from y_0 = v, and in a
- * midpoint step without substeps on a grid of at least 2^24 points, or in
- * mode 5, it also forms the stage vector A u + S itself); where those
- * forms do not apply it computes terms k+1 and
- * k+2 in one launch, keeping y_{k+1} on chip, with the input rows staged in
- * LDS from 2^20 points on and one-row frames in registers below;
+ * default) computes up to seven terms per launch, the first launch included,
+ * as a pipeline of waves along the rows (y_{k+1} .. y_{k+6} and the p between
+ * handed on through LDS; read y_k, the fields and p_k once, write y_{k+7} and
+ * p_{k+7}); a midpoint step without substeps forms its stage vector A u + S in
+ * the first launch.  On grids of 2^28 points and more it computes three (mode
+ * 5's form; with FP64 Newton vectors and no augmented column among terms
+ * 1 .. 3 the first launch takes three terms too and forms the stage vector),
+ * or where that does not apply two in mode 2's form;
  * mode = 2 and mode = 3
  * force the two-term LDS-staged and register-frame forms; mode = 4 computes four
  * terms per launch (y_{k+1} .. y_{k+3} kept in LDS, three-row frames), on
  * grids swept without non-temporal hints and, on a periodic grid, ny >= 4
- * other than 5 and 9 (a block's rows wrap once; ADL_EINVAL otherwise; mode 1
- * then runs two terms per launch); mode = 5 computes three terms per launch
+ * other than 5 and 9 (a block's rows wrap once; ADL_EINVAL otherwise);
+ * mode = 5 computes three terms per launch
  * with the input rows staged in LDS (y_{k+1}, y_{k+2} kept in LDS), on grids
  * whose two-term tiling has two columns per lane (ADL_EINVAL otherwise);
  * mode = 6 computes four terms per launch with the input rows staged in LDS
  * (y_{k+1} .. y_{k+3} kept in LDS; nx even and at least 128, ADL_EINVAL
  * otherwise); mode = 0 launches one kernel per term.
- * A fused launch stores y and p of its last term only; when the sweep stops
- * at an earlier term of a launch, the launch is run again on its inputs to
+ * A fused launch stores y and p of its last term only (mode 1: also p of the
+ * degree the plan last took); when the sweep stops at another term of a launch, the launch is run again on its inputs to
  * store p of that term (the same arithmetic, so the same values).  Results
  * agree to rounding (the block partial sums of the norms are grouped
  * differently).  ADL_EINVAL for other values. */

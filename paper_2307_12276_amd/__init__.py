@@ -271,8 +271,8 @@ class Op:
         _check(lib().adl_op_set_tiling(self.handle, int(rows), int(cols_per_lane)))
 
     def set_term_fusion(self, mode=True):
-        """Newton terms per launch: True/1 the library's choice (four below
-        2^20 points, else three), 2 two with LDS-staged rows, 3 two with
+        """Newton terms per launch: True/1 the library's choice (the
+        pipeline, up to seven), 2 two with LDS-staged rows, 3 two with
         register frames, 4 four, 5 three with LDS-staged rows, 6 four with
         LDS-staged rows, False/0 one."""
         m = int(mode) if not isinstance(mode, bool) else int(mode)

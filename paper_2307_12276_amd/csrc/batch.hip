@@ -539,22 +539,6 @@ struct StepRows {
   double p[VEC];
 };
 
-// A copy into fresh registers that the compiler cannot merge with its
-// source: a step copies the rows it was handed before using them, so that
-// their load registers are free again for the loads of the next step,
-// and the loop carries each buffer of loads in flight in the same registers
-// (otherwise the register allocator may copy a register whose load is still
-// in flight at the loop's back edge, and such a copy waits for the load).
-__device__ __forceinline__ float vcopy(float v) {
-  float o;
-  asm("v_mov_b32 %0, %1" : "=v"(o) : "v"(v));
-  return o;
-}
-__device__ __forceinline__ double vcopy(double v) {
-  double o;
-  asm("v_mov_b64 %0, %1" : "=v"(o) : "v"(v));
-  return o;
-}
 template <typename T, int VEC>
 __device__ __forceinline__ TRow<T, VEC> vcopy(const TRow<T, VEC>& x) {
   TRow<T, VEC> o;

@@ -120,6 +120,23 @@ __device__ __forceinline__ void str_s(T* rowp, int col, const double (&c)[VEC]) 
   }
 }
 
+// A copy into fresh registers that the compiler cannot merge with its
+// source: a step copies the rows it was handed before using them, so that
+// their load registers are free again for the loads of the next step,
+// and the loop carries each buffer of loads in flight in the same registers
+// (otherwise the register allocator may copy a register whose load is still
+// in flight at the loop's back edge, and such a copy waits for the load).
+__device__ __forceinline__ float vcopy(float v) {
+  float o;
+  asm("v_mov_b32 %0, %1" : "=v"(o) : "v"(v));
+  return o;
+}
+__device__ __forceinline__ double vcopy(double v) {
+  double o;
+  asm("v_mov_b64 %0, %1" : "=v"(o) : "v"(v));
+  return o;
+}
+
 // Row index after the boundary rule; zero = the whole row is a zero ghost row.
 __device__ __forceinline__ int map_row(int r, int ny, int bc, int mode, bool& zero) {
   zero = false;
@@ -232,6 +249,15 @@ __device__ __forceinline__ void grid_reduce(double (&acc)[NA], double* partials,
   grid_reduce<NA, NS>(acc, partials, ctl, (int)gridDim.x, (int)blockIdx.x, fin);
 }
 
-
+// Dispatch index -> logical block, such that each XCD (the dispatcher deals
+// blocks to the 8 XCDs round-robin) runs a contiguous range of logical blocks:
+// neighbouring strips then share the 128-byte lines at their common edge in
+// one L2 (at 4096^2: 13 % fewer HBM reads).  A bijection on [0, n) that keeps
+// 0 at 0.
+__device__ __forceinline__ int xcd_contiguous(int bid, int n) {
+  const int q = n / 8, rem = n % 8;
+  const int x = bid % 8, l = bid / 8;
+  return x < rem ? x * (q + 1) + l : rem * (q + 1) + (x - rem) * q + l;
+}
 
 }  // namespace adl

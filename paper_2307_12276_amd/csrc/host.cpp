@@ -5,13 +5,14 @@
 // approximated by Newton interpolation of phi_l((c + gamma xi) dt) at Leja
 // points xi in [-2, 2], c = alpha/2, gamma = -alpha/4, applied term by term:
 //   y_{k+1} = ((A - c I)/gamma - xi_k I) y_k,   p_{k+1} = p_k + d_{k+1} y_{k+1}.
-// Two terms per GPU launch after the first (fused stencils + axpys + norms);
+// Up to seven terms per GPU launch (fused stencils + axpys + norms);
 // one block of each launch takes the stopping decision of the previous
 // launch's terms and sets a device stop flag, so that launches enqueued after
 // convergence do no work, and the host learns the outcome once per chunk of
 // launches (by spinning on a pinned host mirror that the chunk's decision
 // launch writes, or by copying the control block back).
 #include "op.h"
+#include "pipe.h"
 
 #include <algorithm>
 #include <atomic>
@@ -206,15 +207,8 @@ static size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 struct WsLayout {
   size_t kxx, kxy, kyy, ax, ay, y0, y1, p, p2, p3, p4, w1, w2, yacc, tmp, tmp2, partials, ctl, total;
 };
-// four Newton terms per launch on grids below this many points (the grid's
-// vectors stay in the caches) ...
-constexpr long kFourTermMaxPoints = 1L << 20;
-// ... which is also the default there: measured on MI355X (FP64, steps/s of
-// the two-stage quadrature, two terms per launch -> four, LDS rows accessed
-// 16 bytes per lane, chunks ending on their targets): 256^2 +7 %, 384^2
-// +15 %, 512^2 +14 %, 640^2 +44 %, 896^2 +31 %, 1000^2 +11 %
-
 // rows of block partials per slot: three per term of a launch of up to four
+// with a tiling's blocks (the pipeline's 21 rows fit too: it has fewer blocks)
 constexpr int kSlotRows = 12;
 
 static size_t max_partial_blocks(int nx, int ny) {
@@ -414,7 +408,6 @@ static double leja_bytes(const adl_op* op, int k, bool with_w2) {
 // launches at 512^2 and at 2048^2, 335 MB; 4-10 % faster at 2896^2 and
 // 4096^2).
 constexpr double kStreamMinBytes = 512.0 * 1024 * 1024;
-constexpr long kStagedMinPoints = 1L << 20;  // two-term launches stage their rows in LDS from here up
 static int streaming_on(const adl_op* op) {
   if (op->streaming >= 0) return op->streaming;
   const double fs = op->f.f32 ? 4.0 : 8.0;
@@ -450,9 +443,10 @@ static bool four_staged_ok(const adl_op* op, int vec) {
 // p_out = g(A) v (top block of the augmented form when w2 != null; the
 // augmented column enters with coefficient s_k * w2scale).
 //
-// Launches: the first term (y_0 = v) alone, then four terms per launch where
-// the op runs the four-term kernel, else two while the op fuses terms (fewer
-// when the degree cap is near; one per launch without fusion).  Each
+// Launches (modes other than the pipeline's): the first term (y_0 = v) alone,
+// then four terms per launch where the op runs a four-term kernel, else three
+// or two while the op fuses terms (fewer when the degree cap is near; one per
+// launch without fusion).  Each
 // launch's block 0 takes the stopping decision of the previous launch's terms
 // from its block partials; a one-block launch at the end of every chunk
 // decides the chunk's last launch, and the host reads the outcome once per
@@ -468,33 +462,216 @@ static bool four_staged_ok(const adl_op* op, int vec) {
 // p buffers are p_out and two workspace vectors, arranged so that the
 // predicted degree ends in p_out; otherwise the result is copied there.
 // Whether a sweep on vectors of tiling T runs three terms per launch with
-// LDS-staged rows (the default from kStagedMinPoints up, or mode 5)
+// LDS-staged rows (mode 5, or the default mode where the pipeline kernel does
+// not apply: pipe_ok)
 static bool three_term_sweep(const adl_op* op, const Tiling& T) {
   const bool fours = op->fuse_terms == 6 && four_staged_ok(op, T.vec);
-  const bool four = !fours && (op->fuse_terms == 4 || (op->fuse_terms == 1 && op->n < kFourTermMaxPoints)) &&
-                    four_terms_ok(op);
+  const bool four = !fours && op->fuse_terms == 4 && four_terms_ok(op);
   return !four && !fours && three_terms_ok(op, T.vec) &&
-         (op->fuse_terms == 5 || (op->fuse_terms == 1 && (long)op->nx * op->ny >= kStagedMinPoints));
+         (op->fuse_terms == 5 || op->fuse_terms == 1);
 }
 
-// Whether a midpoint step folds its stage vector w = A u + s into the
-// sweep's first launch (the four-stage LDS march, terms 1 .. 3): one
-// substep, a three-term sweep with FP64 Newton vectors whose first launch
-// takes three terms, the four-term staged tiling available; by default from
-// kStageFuseMinPoints up (measured, steps/s fused against a stage launch of
-// its own: 4096^2 FP64 +2 %, FP32 fields +0.4 %; 2048^2 -1.2 %, 1024^2
-// -1 %: the four-stage march is latency-bound, and on smaller grids its
-// launch costs about as much as the two it replaces), always in mode 5
-constexpr long kStageFuseMinPoints = 1L << 24;
+// The default mode's sweeps run on the pipeline kernel, which addresses its
+// vectors by 32-bit byte offsets; a grid too large for those (2 GiB a vector)
+// takes the three-term staged kernel.  Both measured (steps of two
+// applications, us, before and with the pipeline): 64^2 779 / 457, 512^2 1808 /
+// 1150, 1001 x 777 with advection fields 1513 / 498, 1024^2 3059 / 1326,
+// 4096^2 10365 / 5649.
+static bool pipe_ok(const adl_op* op) { return op->fuse_terms == 1 && (long)op->nx * op->ny < kPipePoints; }
+
+// Whether a midpoint step folds its stage vector w = A u + s into the sweep's
+// first launch: with one substep, on the pipeline kernel (its first launch has
+// one term less; measured at 64^2 .. 4096^2, it replaces a launch of 3 - 45 us)
+// and, with FP64 Newton vectors, where the first launch of a three-term sweep
+// takes three terms (the four-stage LDS march)
 static bool stage_fusable(const adl_op* op, const double* u, const double* s, double dt) {
-  if (op->storage == ADL_STORAGE_FP32_FIELDS_Y || op->alpha == 0.0 || !op->has_bound) return false;
-  if (op->fuse_terms != 5 && (long)op->nx * op->ny < kStageFuseMinPoints) return false;
+  if (op->alpha == 0.0 || !op->has_bound) return false;
   int K = substeps_for(op->alpha, dt, op->rho_max);
   if (op->learned) K = std::max(K, op->substeps_hint);
+  if (pipe_ok(op)) return K == 1;
+  if (op->storage == ADL_STORAGE_FP32_FIELDS_Y || (op->fuse_terms != 5 && op->fuse_terms != 1)) return false;
   int maxdeg = op->max_degree;
   if (op->learned && op->budget > 0 && op->budget < maxdeg) maxdeg = op->budget;
   const Tiling& T = tiling_for(op, u, s, op->p);
   return K == 1 && maxdeg >= 3 && three_term_sweep(op, T) && four_staged_ok(op, T.vec);
+}
+
+// The same sweep by the pipeline kernel (the default mode): kPipeMax
+// terms per launch, the first launch included; stage_u set: the first launch
+// forms the stage vector v = A stage_u + stage_s as its first stage, ahead of
+// its terms.
+//
+// Chunks: the first one covers the plan's last degree (the first sweep of a
+// plan: a guess from rho h) in whole launches, and the launch that holds the
+// predicted degree stores p of that term too (into p_out; 8 B per point more
+// on one launch), so that a sweep stopping there needs no replay and one
+// stopping a little later no further chunk.
+static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, double w2scale, double* p_out,
+                      double tol, int maxdeg, hipStream_t st, SweepOut& out, const double* stage_u,
+                      const double* stage_s) {
+  const bool ys32 = op->storage == ADL_STORAGE_FP32_FIELDS_Y;
+  const double* y0 = stage_u ? stage_u : v;
+  const double* src = stage_u ? stage_s : (w2 && P.s[0] != 0.0 ? w2 : nullptr);
+  const bool known = P.last_degree > 0;
+  const int predicted =
+      std::max(1, std::min(maxdeg, known ? P.last_degree : (int)(3.5 * std::sqrt(std::fabs(P.alpha) * P.h) + 4.0)));
+  // buffers: launch L reads y from ybuf[L mod 3] and p from pbuf[(L + 2) mod 3]
+  // and writes y to ybuf[(L + 1) mod 3], p to pbuf[L mod 3]
+  double* ws[5] = {op->p, op->p2, op->p3, op->p4, op->tmp2};
+  int wi = 0;
+  auto take_ws = [&]() {
+    while (ws[wi] == p_out || ws[wi] == v || ws[wi] == w2) ++wi;
+    return ws[wi++];
+  };
+  void* ybuf3[3] = {op->ybuf[0], op->ybuf[1], take_ws()};
+  double* pbuf[3];
+  // launch L covers terms first_term(L) + 1 .. first_term(L + 1)
+  const int depth = kPipeMax, lead = depth - (stage_u ? 1 : 0);
+  auto first_term = [&](int L) { return L == 0 ? 0 : std::min(maxdeg, lead + (L - 1) * depth); };
+  auto launch_of = [&](int term) { return term <= lead ? 0 : 1 + (term - lead - 1) / depth; };
+  const int lpred = launch_of(predicted);                 // the launch with the predicted degree
+  const bool inside = first_term(lpred + 1) != predicted;  // ... and whether it runs past it
+  for (int i = 0; i < 3; ++i) pbuf[i] = !inside && i == lpred % 3 ? p_out : take_ws();
+  std::vector<int> lk, ln;
+  PipeArgs a{};
+  a.invg = P.invg;
+  a.f32y = ys32;
+  a.stream = streaming_on(op);
+  a.pair = op->nx % 2 == 0 && al16(y0) && al16(src) && al16(p_out);
+  a.partials = op->partials;
+  a.slot_stride = op->slot_stride;
+  a.tol = tol;
+  a.max_degree = maxdeg;
+  a.ctl = op->ctl;
+  pipe_geometry(op->nx, op->ny, op->f.ax != nullptr, a);
+  // the launch of terms k+1 .. k+n: its inputs, recurrence and stages
+  auto set_launch = [&](int L, int k, int n) {
+    a.first = k == 0;
+    a.stage = k == 0 && stage_u ? 1 : 0;
+    a.nst = n + a.stage;
+    a.yin = k == 0 ? (const void*)y0 : ybuf3[L % 3];
+    a.pin = k == 0 ? nullptr : pbuf[(L + 2) % 3];
+    a.src = k == 0 ? src : nullptr;
+    a.srcc = P.s[0] * w2scale;
+    // (a stage vector w: p = 0 + d_0 w)
+    a.d0 = a.stage ? 0.0 : P.d[0];
+    a.shift[0] = 0.0;
+    a.dk[0] = P.d[0];
+    for (int t = 0; t < n; ++t) {
+      a.shift[t + a.stage] = P.shift[k + t];
+      a.dk[t + a.stage] = P.d[k + t + 1];
+    }
+    for (double*& p : a.pst) p = nullptr;
+  };
+  LejaArgs dec{};  // the launch deciding a chunk's last launch
+  dec.tol = tol;
+  dec.max_degree = maxdeg;
+  dec.partials = op->partials;
+  dec.slot_stride = op->slot_stride;
+  dec.ctl = op->ctl;
+  int kcov = 0, L = 0;
+  while (true) {
+    const int target = std::min(maxdeg, kcov == 0 ? predicted : known ? kcov + 1 : kcov + std::max(8, kcov / 4));
+    const int L0 = L;
+    while (kcov < target) {
+      const int n = first_term(L + 1) - kcov;
+      a.ev_start = a.ev_stop = nullptr;
+      if (op->prof) {
+        while ((int)op->evs.size() < 2 * (L - L0 + 1)) {
+          hipEvent_t e;
+          HIPCHK(hipEventCreate(&e));
+          op->evs.push_back(e);
+        }
+        a.ev_start = op->evs[2 * (L - L0)];
+        a.ev_stop = op->evs[2 * (L - L0) + 1];
+      }
+      set_launch(L, kcov, n);
+      a.yout = ybuf3[(L + 1) % 3];
+      a.pst[a.nst - 1] = pbuf[L % 3];
+      if (inside && L == lpred) a.pst[predicted - kcov - 1 + a.stage] = p_out;
+      a.slot = L & 1;
+      HIPCHK(launch_pipe(op->f, a, st));
+      a.nb_prev = a.nblocks;
+      a.k_prev = kcov;
+      a.nterms_prev = n;
+      a.slot_prev = L & 1;
+      lk.push_back(kcov);
+      ln.push_back(n);
+      kcov += n;
+      ++L;
+    }
+    dec.k = kcov;
+    dec.nb_prev = a.nb_prev;
+    dec.k_prev = a.k_prev;
+    dec.nterms_prev = a.nterms_prev;
+    dec.slot_prev = a.slot_prev;
+    // outcome: published to the host mirror and awaited by spinning, or (when
+    // timing launches with events, which need the stream synchronised, or
+    // without a mirror) copied back
+    const bool spin = op->hctl && op->host_wait && !op->prof;
+    dec.hctl = spin ? op->hctl_dev : nullptr;
+    dec.hseq = spin ? (op->hseq = next_hseq()) : 0;
+    HIPCHK(launch_decide(dec, st));
+    RETCHK(spin ? await_outcome(op, st) : read_ctl(op, st));
+    if (op->prof) {
+      // launches after the one that ran beside the final decision skipped
+      // their work: time the others
+      const bool stopped = op->host_ctl->stop != 0;
+      for (int l = L0; l < L; ++l) {
+        float ms = 0.0f;
+        HIPCHK(hipEventElapsedTime(&ms, op->evs[2 * (l - L0)], op->evs[2 * (l - L0) + 1]));
+        const double b = leja_bytes(op, lk[l], lk[l] == 0 && src);
+        op->prof_ms += ms;
+        op->prof_launches += 1;
+        op->prof_bytes += b;
+        // a launch of more than three terms counts as groups of three and a
+        // remainder, its time and bytes shared out over its terms
+        auto count = [&](int kind, int launches, int terms) {
+          op->kind_ms[kind] += ms * terms / ln[l];
+          op->kind_launches[kind] += launches;
+          op->kind_bytes[kind] += b * terms / ln[l];
+          op->kind_terms[kind] += terms;
+        };
+        const int threes = ln[l] / 3, rest = ln[l] % 3;
+        if (lk[l] == 0) {
+          count(ADL_LAUNCH_FIRST, 1, ln[l]);
+        } else {
+          if (threes) count(ADL_LAUNCH_THREE, threes, 3 * threes);
+          if (rest) count(rest == 1 ? ADL_LAUNCH_ONE : ADL_LAUNCH_TWO, 1, rest);
+        }
+        if (stopped && lk[l] >= op->host_ctl->degree) break;  // ran beside (or after) the final decision
+      }
+    }
+    if (op->host_ctl->stop || kcov >= maxdeg) break;
+  }
+  out.degree = op->host_ctl->degree;
+  out.status = op->host_ctl->stop ? op->host_ctl->status : 3;
+  if (out.status != 1) return ADL_OK;
+  const int m = P.last_degree = out.degree;
+  if (m == 0) {
+    HIPCHK(launch_fill(op->n, p_out, 0.0, st));
+    return ADL_OK;
+  }
+  const int Ls = launch_of(m);
+  double* res = pbuf[Ls % 3];
+  if (inside && m == predicted) {
+    res = p_out;
+  } else if (m != lk[Ls] + ln[Ls]) {
+    // the sweep stopped inside launch Ls: replay it up to term m on its inputs
+    // (intact: the launch beside the decision of launch Ls wrote neither, and
+    // every later one skipped its work), storing p of term m only, into p_out
+    // unless p_out holds its p input
+    const double* pin = Ls == 0 ? nullptr : pbuf[(Ls + 2) % 3];
+    res = pin == p_out ? pbuf[Ls % 3] : p_out;
+    a.ev_start = a.ev_stop = nullptr;
+    set_launch(Ls, lk[Ls], m - lk[Ls]);
+    a.yout = nullptr;
+    a.pst[a.nst - 1] = res;
+    a.replay = 1;
+    HIPCHK(launch_pipe(op->f, a, st));
+  }
+  if (res != p_out) HIPCHK(launch_axpby(op->n, p_out, 1.0, res, 0.0, nullptr, st));
+  return ADL_OK;
 }
 
 static int sweep(adl_op* op, Plan& P, const double* v, const double* w2, double w2scale, double* p_out,
@@ -503,6 +680,7 @@ static int sweep(adl_op* op, Plan& P, const double* v, const double* w2, double 
   // stage_u (v null): the sweep of v = A stage_u + stage_s, whose first
   // launch computes that stage vector itself (stage_fusable)
   if (op->learned && op->budget > 0 && op->budget < maxdeg) maxdeg = op->budget;
+  if (pipe_ok(op)) return pipe_sweep(op, P, v, w2, w2scale, p_out, tol, maxdeg, st, out, stage_u, stage_s);
   // (the control block is cleared by block 0 of the first launch)
   const bool ys32 = op->storage == ADL_STORAGE_FP32_FIELDS_Y;
   const Tiling& T = tiling_for(op, stage_u ? stage_u : v, p_out);
@@ -511,11 +689,9 @@ static int sweep(adl_op* op, Plan& P, const double* v, const double* w2, double 
   const bool fuse = op->fuse_terms != 0;
   // four terms per launch with LDS-staged rows (mode 6)
   const bool fours = op->fuse_terms == 6 && four_staged_ok(op, T.vec);
-  const bool four = !fours && (op->fuse_terms == 4 || (op->fuse_terms == 1 && op->n < kFourTermMaxPoints)) &&
-                    four_terms_ok(op);
-  // three terms per launch (LDS-staged) from kStagedMinPoints up by default
-  // (4096^2 FP64 headline steps: 140 steps/s with two terms per launch, 185
-  // with three), or forced by mode 5
+  const bool four = !fours && op->fuse_terms == 4 && four_terms_ok(op);
+  // three terms per launch (LDS-staged; 4096^2 FP64 headline steps: 140 steps/s
+  // with two terms per launch, 185 with three)
   const bool three = three_term_sweep(op, T);
   const Tiling& T3 = op->t3;
   const Tiling& T4s = op->t4s;
@@ -606,14 +782,9 @@ static int sweep(adl_op* op, Plan& P, const double* v, const double* w2, double 
   a.max_degree = maxdeg;
   a.ystore_f32 = ys32;
   a.stream = streaming_on(op);
-  // two-term kernel: input rows staged in LDS from kStagedMinPoints up (each
-  // input row then leaves memory once per run of bands: 4096^2 FP64 286 ->
-  // 225-234 us per launch); the register-frame kernel on smaller grids,
-  // where the staged kernel's prologue and extra barrier do not pay (measured
-  // per launch, staged / frames: 512^2 1.14, 768^2 0.93-1.05, 1024^2
-  // 0.87-0.92, 1536^2 0.78-0.86, 2048^2 0.84-0.89)
-  a.staged = op->fuse_terms == 2 || op->fuse_terms == 5 || op->fuse_terms == 6 ||
-             (op->fuse_terms == 1 && (long)op->nx * op->ny >= kStagedMinPoints);
+  // two-term launches: input rows staged in LDS (4096^2 FP64: 286 -> 225-234 us
+  // a launch against the register-frame kernel) except in mode 3
+  a.staged = op->fuse_terms == 1 || op->fuse_terms == 2 || op->fuse_terms == 5 || op->fuse_terms == 6;
   a.partials = op->partials;
   a.slot_stride = op->slot_stride;
   a.ctl = op->ctl;

@@ -51,8 +51,8 @@ struct adl_op {
   Tiling t4s{}; // four-term staged kernel: strips of 60*VEC output columns, kMaxGrid3 blocks
   Tiling t4{};  // four-term Newton-Leja kernel (two columns per lane when nx is even)
   Tiling t41{}; // four-term kernel, one column per lane
-  int fuse_terms = 1;  // 0 one Newton term per launch, 1 two (kernel by tiling), 2 two (LDS-staged), 3 two (frames),
-                       // 4 four (grids below 2^20 points)
+  int fuse_terms = 1;  // 0 one Newton term per launch, 1 the pipeline (up to seven), 2 two (LDS-staged), 3 two (frames),
+                       // 4 four (frames), 5 three (LDS-staged), 6 four (LDS-staged)
   int streaming = -1;  // non-temporal hints on Newton vectors: -1 auto, 0 off, 1 on
   int nx = 0, ny = 0, bc = 0, storage = 0;
   double hx = 0, hy = 0;

@@ -1,0 +1,66 @@
+// The pipeline kernels' launch geometry and launcher.
+#include <type_traits>
+
+#include <hip/hip_ext.h>
+
+#include "pipe_kernel.h"
+
+namespace adl {
+
+// One block per CU where that leaves a block at most kPipeRows1 rows, else two:
+// two share a CU's issue slots but halve the rows, and a launch takes rows + 21
+// ticks.  A sweep of 89 terms, us, with 255 / 511 blocks: 256^2 173 / 199, 512^2
+// 213 / 233, 896^2 (29 rows) 313 / 321, 2048 x 512 (40 rows) 365 / 362, 1024^2
+// (41 rows) 369 / 371, 1280^2 466 / 457, 4096^2 step 7430 / 5834.  With
+// advection fields two blocks' LDS (98 KB each) does not fit a CU: 1001 x 777
+// step 486 / 664.
+void pipe_geometry(int nx, int ny, bool advf, PipeArgs& a) {
+  a.ncb = (nx + kPipeCols - 1) / kPipeCols;
+  auto rows = [&](int blocks) {
+    int runs = blocks / a.ncb;
+    if (runs < 1) runs = 1;
+    if (runs > ny) runs = ny;
+    return (ny + runs - 1) / runs;
+  };
+  a.rows = rows(kPipeBlocks1);
+  if (a.rows > kPipeRows1 && !advf) a.rows = rows(kPipeBlocks2);
+  a.nblocks = a.ncb * ((ny + a.rows - 1) / a.rows);
+}
+
+hipError_t launch_pipe(const FieldView& f, const PipeArgs& a, hipStream_t st) {
+  if ((long)f.nx * f.ny >= kPipePoints) return hipErrorInvalidValue;
+  if (a.nst < 1 || a.nst > kPipeMax || a.rows < 1 || a.ncb * kPipeCols < f.nx ||
+      a.nblocks != a.ncb * ((f.ny + a.rows - 1) / a.rows))
+    return hipErrorInvalidValue;
+  // (a replay writes no partials)
+  if (!a.replay && 3L * a.nst * a.nblocks > a.slot_stride) return hipErrorInvalidValue;
+  // a first launch forms its p_0, a later one reads it; the added row and the
+  // stage vector belong to first launches
+  if (a.first ? a.pin != nullptr : (a.pin == nullptr || a.src || a.stage)) return hipErrorInvalidValue;
+  // what is read and what is stored are distinct vectors
+  if (a.yin == nullptr || a.yin == a.yout) return hipErrorInvalidValue;
+  bool any = false;
+  for (int t = 0; t < kPipeMax; ++t) {
+    if (!a.pst[t]) continue;
+    any = true;
+    if (t >= a.nst || a.pst[t] == a.pin || a.pst[t] == a.yin || a.pst[t] == a.yout || a.pst[t] == a.src)
+      return hipErrorInvalidValue;
+    for (int i = 0; i < t; ++i)
+      if (a.pst[i] == a.pst[t]) return hipErrorInvalidValue;
+  }
+  if (!any) return hipErrorInvalidValue;
+  return f.f32 ? launch_pipe_fields<float>(f, a, st) : launch_pipe_fields<double>(f, a, st);
+}
+
+// The decision that closes a chunk, which the host waits for: one block of 16
+// waves, a wave per row of partials (15 rows at seven terms).
+__global__ __launch_bounds__(16 * kWave) void decide_kernel(LejaArgs A) {
+  leja_decide(A);
+  if (A.hctl && threadIdx.x == 0) publish_outcome(A);
+}
+hipError_t launch_decide(const LejaArgs& a, hipStream_t st) {
+  decide_kernel<<<1, 16 * kWave, 0, st>>>(a);
+  return hipGetLastError();
+}
+
+}  // namespace adl

@@ -921,15 +921,4 @@ constexpr size_t staged_lds_bytes() {
          sizeof(double);
 }
 
-// Dispatch index -> logical block, such that each XCD (the dispatcher deals
-// blocks to the 8 XCDs round-robin) runs a contiguous range of logical blocks:
-// neighbouring strips then share the 128-byte lines at their common edge in
-// one L2 (at 4096^2: 13 % fewer HBM reads).  A bijection on [0, n) that keeps
-// 0 at 0.
-__device__ __forceinline__ int xcd_contiguous(int bid, int n) {
-  const int q = n / 8, rem = n % 8;
-  const int x = bid % 8, l = bid / 8;
-  return x < rem ? x * (q + 1) + l : rem * (q + 1) + (x - rem) * q + l;
-}
-
 }  // namespace adl

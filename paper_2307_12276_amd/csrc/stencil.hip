@@ -28,6 +28,7 @@
 // read the stop flag (no agent-scope fence; a kernel boundary makes the
 // partials visible).  Results are bitwise reproducible for a given tiling.
 #include "bounds.h"
+#include "decide.h"
 #include "staged.h"
 
 #include <type_traits>
@@ -37,41 +38,6 @@
 #include <cmath>
 
 namespace adl {
-
-// ---------------------------------------------------------------------------
-// Block-wide fixed-order reduction (sums for k < NS, NaN-propagating max for
-// the rest); every thread receives the totals.
-// ---------------------------------------------------------------------------
-template <int NA, int NS>
-__device__ __forceinline__ void block_allreduce_at(double (&v)[NA], double* sh) {
-#pragma unroll
-  for (int k = 0; k < NA; ++k) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const double t = __shfl_xor(v[k], o);
-      v[k] = (k < NS) ? v[k] + t : nanmax(v[k], t);
-    }
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  __syncthreads();
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < NA; ++k) sh[wave * NA + k] = v[k];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < NA; ++k) {
-    double s = sh[k];
-    for (int w = 1; w < nw; ++w) s = (k < NS) ? s + sh[w * NA + k] : nanmax(s, sh[w * NA + k]);
-    v[k] = s;
-  }
-}
-// the same with a static LDS array (sh: NA * 16 doubles)
-template <int NA, int NS>
-__device__ __forceinline__ void block_allreduce(double (&v)[NA]) {
-  __shared__ double sh[NA * 16];
-  block_allreduce_at<NA, NS>(v, sh);
-}
 
 // Totals of the block partials written by an earlier launch: part[k * nb + b].
 template <int NA, int NS>
@@ -223,108 +189,6 @@ struct LejaEp {
     str_s<NT, double, VEC>(p + ro, g.col0, pn);
   }
 };
-
-// Stopping test of the terms of the previous launch (k_prev+1 ..
-// k_prev+nterms_prev, in order) from its block partials, taken by one block
-// (fixed-order totals) and recorded in the control block unless an earlier
-// launch has already stopped the sweep.
-// (dsh: a kernel's dynamic LDS for the reduction (160 doubles), or null for
-// a static array; the four-term staged kernel passes its rings, so that it
-// holds no static LDS and three blocks fit a CU)
-template <bool DYN = false>
-__device__ __forceinline__ void leja_decide(const LejaArgs& A, double* dsh = nullptr) {
-  // the stop flag travels with the partial sums (a max-reduced value), so its
-  // load and the partial loads are in flight together
-  const double* part = A.partials + (long)A.slot_prev * A.slot_stride;
-  const int nb = A.nb_prev;
-  const int nt = A.nterms_prev;
-  // tn2 / pn2 of terms 1 .. 4 of the decided launch (sums; term t's partials
-  // at rows 3t, 3t + 1), max(|y0|, |w2|) (row 2), flag (max)
-  double v[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  if (threadIdx.x == 0)
-    v[9] = (double)__hip_atomic_load(&A.ctl->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  bool any = false;
-  for (int i = threadIdx.x; i < nb; i += blockDim.x) {
-    v[0] += part[i];
-    v[1] += part[(long)nb + i];
-    const double m = part[2L * nb + i];
-    v[8] = any ? nanmax(v[8], m) : m;
-    if (nt >= 2) {
-      v[2] += part[3L * nb + i];
-      v[3] += part[4L * nb + i];
-    }
-    if (nt >= 3) {
-      v[4] += part[6L * nb + i];
-      v[5] += part[7L * nb + i];
-    }
-    if (nt >= 4) {
-      v[6] += part[9L * nb + i];
-      v[7] += part[10L * nb + i];
-    }
-    any = true;
-  }
-  if constexpr (DYN) block_allreduce_at<10, 8>(v, dsh);
-  else block_allreduce<10, 8>(v);
-  if (v[9] != 0.0) return;  // decided by an earlier launch
-  // Terms up to `done` were decided already: a chunk's closing decision
-  // launch decides the chunk's last launch, and the first launch of the next
-  // chunk is handed the same launch.  Each term enters the window once.
-  const int done = A.ctl->degree;
-  if (A.k_prev + nt <= done) return;
-  // norms of the terms before the decided ones (the window of the test)
-  double hist[kStopHist];
-#pragma unroll
-  for (int i = 0; i < kStopHist; ++i) hist[i] = A.ctl->hist[i];
-  int stop = 0, status = 0, degree = A.k_prev + A.nterms_prev;
-  double tn2 = 0.0, pn2 = 0.0;
-  for (int t = 0; t < nt && !stop; ++t) {
-    const int deg = A.k_prev + t + 1;
-    if (deg <= done) continue;
-    tn2 = v[2 * t];
-    pn2 = v[2 * t + 1];
-    if (!isfinite(tn2) || !isfinite(pn2)) {
-      stop = 1; status = 2; degree = deg;
-    } else if (deg == 1 && v[8] == 0.0) {
-      stop = 1; status = 1; degree = 0;
-    } else if (window_stop(hist, deg, sqrt(tn2), pn2, A.tol)) {
-      stop = 1; status = 1; degree = deg;
-    } else if (deg >= A.max_degree) {
-      stop = 1; status = 3; degree = deg;
-    }
-  }
-  if (threadIdx.x == 0) {
-    Ctl* c = A.ctl;
-    c->tn2 = tn2;
-    c->pn2 = pn2;
-#pragma unroll
-    for (int i = 0; i < kStopHist; ++i) c->hist[i] = hist[i];
-    c->degree = degree;
-    c->status = status;
-    __hip_atomic_store(&c->stop, stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-}
-
-// The sweep's outcome for the host (thread 0 of the decision launch, after
-// leja_decide): the control block's fields (written by this thread, or by an
-// earlier launch), then the sequence number with a system-scope release, so
-// that a host that sees the number sees the fields too.
-__device__ __forceinline__ void publish_outcome(const LejaArgs& A) {
-  HostCtl* h = A.hctl;
-  const Ctl* c = A.ctl;
-  h->stop = __hip_atomic_load(&c->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  h->status = c->status;
-  h->degree = c->degree;
-  __hip_atomic_store(&h->seq, A.hseq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-// The sweep's stop flag, read once per block (thread 0) and broadcast, so that
-// a concurrent update of the flag cannot split a block.
-__device__ __forceinline__ bool block_stopped(const Ctl* ctl) {
-  __shared__ int s_stop;
-  if (threadIdx.x == 0) s_stop = __hip_atomic_load(&ctl->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-  return s_stop != 0;
-}
 
 // One Newton-Leja term, launch k: y_{k+1} from y_k, p_{k+1} = p_k + d_{k+1} y_{k+1}
 // into the other p buffer, block partials of the norms.
