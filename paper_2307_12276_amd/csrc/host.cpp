@@ -1379,6 +1379,68 @@ int adl_apply(adl_op* op, const double* x, double* y, void* stream) {
   return ADL_OK;
 }
 
+// Power iteration on the pipeline kernel: kPipeMax applications a launch as
+// Newton terms without a shift, y_k = A y_{k-1} / s, whose norms give
+// lambda_k = s ||y_k|| / ||y_{k-1}||; s is the Gershgorin bound in the first
+// chunk and the last lambda after it, so that the norms stay in range.  A chunk
+// of launches ends with one block's tests of all its iterations, in order
+// (power_decide_kernel), and the host reads the outcome.  Four launches in the
+// first chunk, eight in the later ones: the method takes 20 - 60 iterations at
+// the default rtol, and a chunk's tail past the stop costs less than a launch
+// and a reading of the host per test.  1024^2: 613 us with an application a
+// launch (10 us, every block summing the 2048 partials of the one before),
+// 168 us.  Grids past the pipeline's 32-bit offsets keep the former.
+static int power_pipe(adl_op* op, double ag, int max_iter, double rtol, uint64_t seed, hipStream_t st) {
+  const Tiling& T = op->t;
+  // the start vector's partials end the second slot; the chunk's come before
+  double* init = op->partials + 2 * op->slot_stride - 3L * T.nblocks;
+  HIPCHK(launch_power_init(T, op->n, seed, op->tmp, init, st));
+  PipeArgs a{};
+  pipe_geometry(op->nx, op->ny, op->f.ax != nullptr, a);
+  const long room = (init - op->partials) / (3L * kPipeMax * a.nblocks);
+  a.pair = op->nx % 2 == 0;
+  a.stream = streaming_on(op);
+  a.slot_stride = op->slot_stride;
+  a.ctl = op->ctl;
+  for (double& d : a.dk) d = 1.0;  // (p, a by-product, is the sum of the y)
+  double* y[2] = {op->tmp, op->tmp2};
+  double* p[2] = {op->p, op->p2};
+  double scale = ag != 0.0 ? std::fabs(ag) : 1.0;
+  int done = 0;
+  for (int L = 0;;) {
+    const int chunk = (int)std::min<long>({(long)(max_iter - done), kPipeMax * room, kPipeMax * (L == 0 ? 4L : 8L)});
+    a.invg = 1.0 / scale;
+    PowerDecide d{};
+    d.partials = op->partials;
+    d.init = L == 0 ? init + 2L * T.nblocks : nullptr;
+    d.ninit = T.nblocks;
+    for (int k = 0, i = 0; k < chunk; ++i, ++L) {
+      a.nst = std::min(kPipeMax, chunk - k);
+      a.first = L == 0;
+      a.yin = y[L & 1];
+      a.yout = y[(L + 1) & 1];
+      a.pin = L == 0 ? nullptr : p[(L + 1) & 1];
+      for (double*& q : a.pst) q = nullptr;
+      a.pst[a.nst - 1] = p[L & 1];
+      a.partials = op->partials + 3L * kPipeMax * a.nblocks * i;
+      HIPCHK(launch_pipe(op->f, a, st));
+      k += a.nst;
+    }
+    d.nb = a.nblocks;
+    d.k = done;
+    d.iters = chunk;
+    d.scale = scale;
+    d.rtol = rtol;
+    d.max_iter = max_iter;
+    d.ctl = op->ctl;
+    HIPCHK(launch_power_decide(d, st));
+    RETCHK(read_ctl(op, st));
+    done += chunk;
+    if (op->host_ctl->stop || done >= max_iter) return ADL_OK;
+    scale = op->host_ctl->lam;
+  }
+}
+
 int adl_spectral_bound(adl_op* op, int method, int max_iter, double rtol, uint64_t seed, double* alpha_out,
                        int* iters_out, void* stream) {
   RETCHK(check_op(op));
@@ -1392,33 +1454,37 @@ int adl_spectral_bound(adl_op* op, int method, int max_iter, double rtol, uint64
   if (method == ADL_BOUND_POWER) {
     if (max_iter < 1) return fail(ADL_EINVAL, "max_iter must be >= 1");
     if (!(rtol > 0.0)) return fail(ADL_EINVAL, "rtol must be > 0");
-    HIPCHK(launch_ctl_reset(op->ctl, 1, st));
-    const Tiling& T = op->t;
-    HIPCHK(launch_power_init(T, op->n, seed, op->tmp, op->partials, st));
-    double* bufs[2] = {op->tmp, op->tmp2};
-    PowerArgs pa{};
-    pa.rtol = rtol;
-    pa.max_iter = max_iter;
-    pa.nb = T.nblocks;
-    pa.partials = op->partials;
-    pa.ctl = op->ctl;
-    int launched = 0;
-    while (true) {
-      const int chunk = std::min(max_iter - launched, launched == 0 ? 64 : 128);
-      for (int i = 0; i < chunk; ++i) {
-        const int k = launched + i;
-        pa.x = bufs[k & 1];
-        pa.w = bufs[(k + 1) & 1];
-        pa.k = k;
-        pa.decide_only = 0;
+    if ((long)op->nx * op->ny < kPipePoints) {
+      RETCHK(power_pipe(op, ag, max_iter, rtol, seed, st));
+    } else {
+      HIPCHK(launch_ctl_reset(op->ctl, 1, st));
+      const Tiling& T = op->t;
+      HIPCHK(launch_power_init(T, op->n, seed, op->tmp, op->partials, st));
+      double* bufs[2] = {op->tmp, op->tmp2};
+      PowerArgs pa{};
+      pa.rtol = rtol;
+      pa.max_iter = max_iter;
+      pa.nb = T.nblocks;
+      pa.partials = op->partials;
+      pa.ctl = op->ctl;
+      int launched = 0;
+      while (true) {
+        const int chunk = std::min(max_iter - launched, launched == 0 ? 64 : 128);
+        for (int i = 0; i < chunk; ++i) {
+          const int k = launched + i;
+          pa.x = bufs[k & 1];
+          pa.w = bufs[(k + 1) & 1];
+          pa.k = k;
+          pa.decide_only = 0;
+          HIPCHK(launch_power_step(op->f, T, pa, st));
+        }
+        launched += chunk;
+        pa.k = launched;
+        pa.decide_only = 1;
         HIPCHK(launch_power_step(op->f, T, pa, st));
+        RETCHK(read_ctl(op, st));
+        if (op->host_ctl->stop || launched >= max_iter) break;
       }
-      launched += chunk;
-      pa.k = launched;
-      pa.decide_only = 1;
-      HIPCHK(launch_power_step(op->f, T, pa, st));
-      RETCHK(read_ctl(op, st));
-      if (op->host_ctl->stop || launched >= max_iter) break;
     }
     const Ctl& c = *op->host_ctl;
     if (c.status == 2) return fail(ADL_ENAN, "non-finite value in power iteration");

@@ -59,6 +59,20 @@ struct PipeArgs {
 void pipe_geometry(int nx, int ny, bool advf, PipeArgs& a);
 // a launch's block partials take 3 x nst x nblocks values of its slot
 hipError_t launch_pipe(const FieldView& f, const PipeArgs& a, hipStream_t st);
+// The power method's tests of iterations k + 1 .. k + iters: launch i of the
+// chunk (kPipeMax iterations, the last one maybe fewer) left its partials at
+// partials + 3 kPipeMax nb i, ||y_0||^2 of the first chunk is the sum of
+// init[0 .. ninit) (else ctl->tn2).  lambda_j = scale ||y_j|| / ||y_{j-1}||.
+struct PowerDecide {
+  const double* partials;
+  const double* init;
+  int ninit, nb;
+  int k, iters;
+  double scale, rtol;
+  int max_iter;
+  Ctl* ctl;
+};
+hipError_t launch_power_decide(const PowerDecide& a, hipStream_t st);
 // the decision of launch slot_prev alone, published to the host mirror if hctl is set
 hipError_t launch_decide(const LejaArgs& a, hipStream_t st);
 

@@ -63,4 +63,54 @@ hipError_t launch_decide(const LejaArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
+// One wave per iteration's sum, then the tests in order: iteration j stops the
+// method where lambda_j is not finite, is zero, or differs from lambda_{j-1} (0
+// before the first) by at most rtol lambda_j.
+constexpr int kPowerIters = 8 * kPipeMax;  // most iterations of a chunk
+__global__ __launch_bounds__(16 * kWave) void power_decide_kernel(PowerDecide A) {
+  __shared__ double n2[kPowerIters + 1];
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  for (int j = wave; j <= A.iters; j += 16) {
+    // (j = 0: the chunk's start vector)
+    const double* p = j == 0 ? A.init : A.partials + (3L * kPipeMax * ((j - 1) / kPipeMax) + 3 * ((j - 1) % kPipeMax)) * A.nb;
+    const int n = j == 0 ? (A.init ? A.ninit : 0) : A.nb;
+    double v = 0.0;
+#pragma unroll 8
+    for (int i = lane; i < n; i += kWave) v += p[i];
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (lane == 0) n2[j] = j == 0 && !A.init ? A.ctl->tn2 : v;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  Ctl* c = A.ctl;
+  double lam = c->lam, lam_prev = c->lam_prev;  // (zero in the first chunk)
+  int stop = 0, status = 0, k = A.k;
+  for (int j = 1; j <= A.iters && !stop; ++j) {
+    ++k;
+    lam_prev = lam;
+    lam = n2[j] == 0.0 ? 0.0 : A.scale * sqrt(n2[j] / n2[j - 1]);
+    if (!isfinite(lam)) {
+      stop = 1; status = 2;
+    } else if (lam == 0.0) {
+      stop = 1; status = 1;
+    } else if (fabs(lam - lam_prev) <= A.rtol * lam) {
+      stop = 1; status = 1;
+    } else if (k >= A.max_iter) {
+      stop = 1; status = 3;
+    }
+  }
+  c->tn2 = n2[A.iters];
+  c->lam = lam;
+  c->lam_prev = lam_prev;
+  c->iters = k;
+  c->status = status;
+  c->stop = stop;
+}
+hipError_t launch_power_decide(const PowerDecide& a, hipStream_t st) {
+  if (a.iters < 1 || a.iters > kPowerIters) return hipErrorInvalidValue;
+  power_decide_kernel<<<1, 16 * kWave, 0, st>>>(a);
+  return hipGetLastError();
+}
+
 }  // namespace adl

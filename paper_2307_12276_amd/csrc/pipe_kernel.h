@@ -582,7 +582,7 @@ __global__ __launch_bounds__(kPipeThreads, ADVF ? 2 : 4) void pipe_kernel(FieldV
         *A.ctl = c;
       }
     } else {
-      if (!A.replay) leja_decide<true>(A, lds);
+      if (!A.replay && A.nterms_prev > 0) leja_decide<true>(A, lds);
     }
     return;
   }
