@@ -47,7 +47,8 @@ __device__ __forceinline__ void block_allreduce(double (&v)[NA]) {
 // already stopped the sweep.  Args: LejaArgs or PipeArgs.
 //
 // Term t's partials are rows 3t (||d y||^2) and 3t + 1 (||p||^2) of the slot;
-// row 2 is max(|y_0|, |w2|) of a sweep's first launch.  A wave takes one
+// row 2 of a sweep's first launch is max(|y_0|, |w2|), or 1 where either is not
+// zero (only zero is told from the rest).  A wave takes one
 // segment of a row at a time (fixed order: lanes, shuffle tree, segments), so
 // that the rows' loads and shuffles run side by side: the decision closing a
 // chunk is on the host's critical path.

@@ -54,6 +54,10 @@ struct PipeArgs {
   int max_degree;
   Ctl* ctl;
   hipEvent_t ev_start, ev_stop;
+  // stage t's shift, d and p array
+  __host__ __device__ double shift_of(int t) const { return shift[t - 1]; }
+  __host__ __device__ double dk_of(int t) const { return dk[t - 1]; }
+  __host__ __device__ double* p_of(int t) const { return pst[t - 1]; }
 };
 // rows, ncb and nblocks of a launch on an nx x ny grid
 void pipe_geometry(int nx, int ny, bool advf, PipeArgs& a);

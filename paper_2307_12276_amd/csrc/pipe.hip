@@ -28,7 +28,8 @@ void pipe_geometry(int nx, int ny, bool advf, PipeArgs& a) {
 }
 
 hipError_t launch_pipe(const FieldView& f, const PipeArgs& a, hipStream_t st) {
-  if ((long)f.nx * f.ny >= kPipePoints) return hipErrorInvalidValue;
+  // (float Newton vectors come with float fields)
+  if ((long)f.nx * f.ny >= kPipePoints || (a.f32y && !f.f32)) return hipErrorInvalidValue;
   if (a.nst < 1 || a.nst > kPipeMax || a.rows < 1 || a.ncb * kPipeCols < f.nx ||
       a.nblocks != a.ncb * ((f.ny + a.rows - 1) / a.rows))
     return hipErrorInvalidValue;

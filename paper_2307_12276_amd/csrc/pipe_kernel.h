@@ -51,8 +51,9 @@ namespace adl {
 
 constexpr int kPipeRow = kWave * 2;  // doubles of an LDS row
 
-// first launches: none, p_0 = d0 y_0, the same with an added row (src)
-enum { PIPE_LATER = 0, PIPE_FIRST = 1, PIPE_FIRST_SRC = 2 };
+// a launch's MODE: a later one, or a first one (p_0 = d0 y_0), maybe with an
+// added row (src) and with the stage vector as its first stage
+enum { PIPE_LATER = 0, PIPE_FIRST = 1, PIPE_SRC = 2, PIPE_STAGE = 4 };
 
 __device__ __forceinline__ void pipe_put(double* row, const double (&c)[2]) {
   typedef double d2 __attribute__((ext_vector_type(2)));
@@ -72,8 +73,9 @@ __device__ __forceinline__ void pipe_get(const double* row, double (&c)[2]) {
 // the scalar offset, the lane's column as a 32-bit vector offset, so a load
 // takes no address arithmetic.  Arrays are limited to 2 GiB (launch_pipe).
 typedef __amdgpu_buffer_rsrc_t PipeRsrc;
+// (a null array has no records: its loads give zero)
 __device__ __forceinline__ PipeRsrc pipe_rsrc(const void* p) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffff, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, p ? 0x7fffffff : 0, 0x00020000);
 }
 constexpr int kPipeDrop = (int)0x80000000u;  // a vector offset past every array: the store is dropped
 
@@ -223,7 +225,8 @@ struct PipeRun {
   unsigned riml;
   int col0;  // the lane's first column
 };
-__device__ __forceinline__ PipeRun pipe_run(const FieldView& F, const PipeArgs& A, int b) {
+template <class Args>
+__device__ __forceinline__ PipeRun pipe_run(const FieldView& F, const Args& A, int b) {
   PipeRun r;
   const int cb = b % A.ncb, run = b / A.ncb;
   r.nst = A.nst;
@@ -251,8 +254,8 @@ __device__ __forceinline__ void pipe_inside(const FieldView& F, const PipeRun& r
 }
 
 // Wave 0: the rows a0 .. J1 - 1 + nst into LDS.
-template <typename TF, typename TYI, bool ADVF, bool PAIR, bool NT, int MODE>
-__device__ __forceinline__ void pipe_loader(const FieldView& F, const PipeArgs& A, double* lds, const PipeRun& r) {
+template <typename TF, typename TYI, bool ADVF, bool PAIR, bool NT, int MODE, class Args>
+__device__ __forceinline__ void pipe_loader(const FieldView& F, const Args& A, double* lds, const PipeRun& r) {
   const int lane = threadIdx.x & (kWave - 1);
   const bool per = F.bc == BC_PERIODIC;
   constexpr int NC = kPipeCoef<ADVF>;
@@ -271,7 +274,7 @@ __device__ __forceinline__ void pipe_loader(const FieldView& F, const PipeArgs& 
   if constexpr (PAIR) cl[0] &= ~1;  // (a clamped pair starts on the even column)
   const PipeRsrc rm = pipe_rsrc(F.kxy), rk = pipe_rsrc(F.kxx), rg = pipe_rsrc(F.kyy), ry = pipe_rsrc(A.yin);
   const PipeRsrc rax = pipe_rsrc(ADVF ? F.ax : F.kxx), ray = pipe_rsrc(ADVF ? F.ay : F.kyy);
-  const PipeRsrc rp = pipe_rsrc(MODE == PIPE_FIRST_SRC ? (const void*)A.src : (const void*)A.pin);
+  const PipeRsrc rp = pipe_rsrc((MODE & PIPE_SRC) ? (const void*)A.src : (const void*)A.pin);
   // the row to load next: running (rr), after the boundary rule (rw), and the
   // two before it (rows past the last one needed, which no stage reads, repeat
   // it); offsets in elements
@@ -301,7 +304,7 @@ __device__ __forceinline__ void pipe_loader(const FieldView& F, const PipeArgs& 
       pipe_load<PAIR, false>(ray, cl, o * SF, s.ay);
     }
     pipe_load<PAIR, false>(ry, cl, o1 * SY, s.y);
-    if constexpr (MODE != PIPE_FIRST) pipe_load<PAIR, NT>(rp, cl, o2 * 8, s.p);
+    if constexpr (MODE == PIPE_LATER || (MODE & PIPE_SRC)) pipe_load<PAIR, NT>(rp, cl, o2 * 8, s.p);
     o2 = o1;
     o1 = o;
     const int step = left_to_load > 0 ? 1 : 0;
@@ -330,7 +333,7 @@ __device__ __forceinline__ void pipe_loader(const FieldView& F, const PipeArgs& 
         ay[v] = (double)vcopy(s.ay.c[v]);
       }
       y[v] = (double)vcopy(s.y.c[v]);
-      if constexpr (MODE != PIPE_FIRST) p[v] = vcopy(s.p.c[v]);
+      if constexpr (MODE == PIPE_LATER || (MODE & PIPE_SRC)) p[v] = vcopy(s.p.c[v]);
     }
     load(s);
     if ((unsigned)(row + r.rimb) >= r.riml || (unsigned)(row - 1 + r.rimb) >= r.riml) {
@@ -373,7 +376,7 @@ __device__ __forceinline__ void pipe_loader(const FieldView& F, const PipeArgs& 
       pipe_put(f + 4 * kPipeRow, ay);
     }
     pipe_put(yb + par, y);
-    if constexpr (MODE == PIPE_FIRST_SRC) pipe_put(wb + par, p);
+    if constexpr ((MODE & PIPE_SRC) != 0) pipe_put(wb + par, p);
     if constexpr (MODE != PIPE_LATER) {
 #pragma unroll
       for (int v = 0; v < 2; ++v) {
@@ -398,9 +401,10 @@ __device__ __forceinline__ void pipe_loader(const FieldView& F, const PipeArgs& 
   for (; m < r.nticks; ++m) __syncthreads();
 }
 
-// Wave t: stage t of the run's rows.
-template <typename TY, bool ADVF, bool PAIR, bool NT, int MODE>
-__device__ __forceinline__ void pipe_stage(const FieldView& F, const PipeArgs& A, double* lds, const PipeRun& r, int t,
+// Wave t: stage t of the run's rows (MODE PIPE_LATER: any but a first launch's
+// stage 1, which takes the added row, forms the stage vector and whether y_0 is zero).
+template <typename TY, bool ADVF, bool PAIR, bool NT, int MODE, class Args>
+__device__ __forceinline__ void pipe_stage(const FieldView& F, const Args& A, double* lds, const PipeRun& r, int t,
                                            int b) {
   const int lane = threadIdx.x & (kWave - 1);
   constexpr int NC = kPipeCoef<ADVF>;
@@ -418,21 +422,20 @@ __device__ __forceinline__ void pipe_stage(const FieldView& F, const PipeArgs& A
     cs[v] = c >= 0 && c < F.nx && lane >= kPipeFrame && lane < kWave - kPipeFrame ? c : kPipeDrop / 8;
   }
   const double ig = A.invg;
-  const double shift = A.shift[t - 1], dk = A.dk[t - 1];
-  const bool wants_max = MODE != PIPE_LATER && t == 1;
-  const bool has_src = MODE == PIPE_FIRST_SRC && t == 1;
-  const bool stagevec = wants_max && A.stage;
-  const double srcc = MODE == PIPE_FIRST_SRC ? A.srcc : 0.0;
+  const double shift = A.shift_of(t), dk = A.dk_of(t);
+  constexpr bool wants_max = MODE != PIPE_LATER, has_src = (MODE & PIPE_SRC) != 0, stagevec = (MODE & PIPE_STAGE) != 0;
+  const double srcc = has_src ? A.srcc : 0.0;
   const double axc = F.axc, ayc = F.ayc;
   // what the stage stores
-  double* pout = A.pst[t - 1];
+  double* pout = A.p_of(t);
   void* yout = t == nst ? A.yout : nullptr;
   __asm__ volatile("" : "+s"(yout), "+s"(pout));  // (held, not loaded again at every store)
   const int flags = __builtin_amdgcn_readfirstlane((t < nst ? 1 : 0) | (yout || pout ? 2 : 0));
   PipeWin win{};
   PipeCoef c1{}, c2{}, nx{};  // indices e - 1, e - 2; the next tick's e
   double hold[2] = {};        // p of the last row
-  double yn2[2] = {}, pn2[2] = {}, ymax[2] = {};
+  double yn2[2] = {}, pn2[2] = {};
+  unsigned some[2] = {};  // bits of the y_0 (and src) seen, without their signs
   // first tick (an even one, maybe a tick before the rows are there: the
   // windows are whole again by the first complete row), last tick with work
   const int n0 = (3 * t - 1) & ~1, n1 = r.J1 - r.J0 + 2 * nst + t;
@@ -503,7 +506,11 @@ __device__ __forceinline__ void pipe_stage(const FieldView& F, const PipeArgs& A
       for (int v = 0; v < 2; ++v) {
         yn2[v] = __builtin_fma(y[v], y[v], yn2[v]);
         pn2[v] = __builtin_fma(pn[v], pn[v], pn2[v]);
-        if (wants_max) ymax[v] = nanmax(ymax[v], A.stage ? fabs(y[v]) : nanmax(fabs(cc[v]), fabs(s[v])));
+        if constexpr (wants_max) {
+          const double a0 = stagevec ? y[v] : cc[v];
+          some[v] |= (unsigned)__double2hiint(a0) << 1 | (unsigned)__double2loint(a0);
+          if (has_src && !stagevec) some[v] |= (unsigned)__double2hiint(s[v]) << 1 | (unsigned)__double2loint(s[v]);
+        }
       }
       if (fl & 2) {
         const int o = row * F.nx;
@@ -539,21 +546,21 @@ __device__ __forceinline__ void pipe_stage(const FieldView& F, const PipeArgs& A
   for (; n < r.nticks; ++n) __syncthreads();
   if (A.replay) return;
 
-  // the stage's partials: term t of the launch at rows 3t, 3t + 1, 3t + 2 (the
-  // latter max(|y_0|, |src|) of a first launch, in the first term's)
+  // the stage's partials: term t of the launch at rows 3t, 3t + 1; row 2 of a
+  // first launch: whether any y_0 or src is not zero (the test needs no more)
   double acc[3] = {0.0, 0.0, 0.0};
 #pragma unroll
   for (int v = 0; v < 2; ++v) {
     if (cs[v] < 0) continue;  // (not an own column)
     acc[0] += yn2[v];
     acc[1] += pn2[v];
-    acc[2] = nanmax(acc[2], ymax[v]);
+    if (some[v]) acc[2] = 1.0;
   }
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) {
     acc[0] += __shfl_xor(acc[0], o);
     acc[1] += __shfl_xor(acc[1], o);
-    if constexpr (MODE != PIPE_LATER) acc[2] = nanmax(acc[2], __shfl_xor(acc[2], o));
+    if constexpr (MODE != PIPE_LATER) acc[2] = fmax(acc[2], __shfl_xor(acc[2], o));
   }
   if (lane == 0) {
     double* const part = A.partials + (long)A.slot * A.slot_stride;
@@ -562,9 +569,8 @@ __device__ __forceinline__ void pipe_stage(const FieldView& F, const PipeArgs& A
     if (term >= 0) {
       part[3L * term * nb + b] = acc[0] * dk * dk;
       part[(3L * term + 1) * nb + b] = acc[1];
-      if (term > 0 || MODE == PIPE_LATER) part[(3L * term + 2) * nb + b] = 0.0;
     }
-    if (MODE != PIPE_LATER && t == 1) part[2 * nb + b] = acc[2];
+    if (wants_max) part[2 * nb + b] = acc[2];
   }
 }
 
@@ -603,13 +609,14 @@ __global__ __launch_bounds__(kPipeThreads, ADVF ? 2 : 4) void pipe_kernel(FieldV
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   using TYI = std::conditional_t<MODE == PIPE_LATER, TY, double>;
   if (wave == 0) pipe_loader<TF, TYI, ADVF, PAIR, NT, MODE>(F, A, lds, r);
-  else pipe_stage<TY, ADVF, PAIR, NT, MODE>(F, A, lds, r, wave, L - 1);
+  else if (MODE != PIPE_LATER && wave == 1) pipe_stage<TY, ADVF, PAIR, NT, MODE>(F, A, lds, r, 1, L - 1);
+  else pipe_stage<TY, ADVF, PAIR, NT, PIPE_LATER>(F, A, lds, r, wave, L - 1);
 }
 
 template <typename TF, typename TY, bool ADVF, bool PAIR, bool NT, int MODE>
 static hipError_t pipe_go(const FieldView& f, const PipeArgs& a, hipStream_t st) {
   const dim3 grid(a.nblocks + 1), blk(kWave * (1 + a.nst));
-  const size_t lds = pipe_lds_bytes(a.nst, ADVF, MODE == PIPE_FIRST_SRC);
+  const size_t lds = pipe_lds_bytes(a.nst, ADVF, (MODE & PIPE_SRC) != 0);
   auto* k = pipe_kernel<TF, TY, ADVF, PAIR, NT, MODE>;
   if (a.ev_start) hipExtLaunchKernelGGL(k, grid, blk, lds, st, a.ev_start, a.ev_stop, 0, f, a);
   else hipLaunchKernelGGL(k, grid, blk, lds, st, f, a);
@@ -626,14 +633,20 @@ static hipError_t pipe_vectors(const FieldView& f, const PipeArgs& a, hipStream_
 template <typename TF, typename TY, bool ADVF>
 static hipError_t pipe_mode(const FieldView& f, const PipeArgs& a, hipStream_t st) {
   if (!a.first) return pipe_vectors<TF, TY, ADVF, PIPE_LATER>(f, a, st);
-  if (a.src) return pipe_vectors<TF, TY, ADVF, PIPE_FIRST_SRC>(f, a, st);
+  if (a.stage) {
+    if (a.src) return pipe_vectors<TF, TY, ADVF, PIPE_FIRST | PIPE_STAGE | PIPE_SRC>(f, a, st);
+    return pipe_vectors<TF, TY, ADVF, PIPE_FIRST | PIPE_STAGE>(f, a, st);
+  }
+  if (a.src) return pipe_vectors<TF, TY, ADVF, PIPE_FIRST | PIPE_SRC>(f, a, st);
   return pipe_vectors<TF, TY, ADVF, PIPE_FIRST>(f, a, st);
 }
 
 template <typename TF>
 hipError_t launch_pipe_fields(const FieldView& f, const PipeArgs& a, hipStream_t st) {
-  if (f.ax) return a.f32y ? pipe_mode<TF, float, true>(f, a, st) : pipe_mode<TF, double, true>(f, a, st);
-  return a.f32y ? pipe_mode<TF, float, false>(f, a, st) : pipe_mode<TF, double, false>(f, a, st);
+  if constexpr (sizeof(TF) == 4) {
+    if (a.f32y) return f.ax ? pipe_mode<TF, float, true>(f, a, st) : pipe_mode<TF, float, false>(f, a, st);
+  }
+  return f.ax ? pipe_mode<TF, double, true>(f, a, st) : pipe_mode<TF, double, false>(f, a, st);
 }
 
 }  // namespace adl
