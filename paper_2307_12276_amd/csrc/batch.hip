@@ -29,6 +29,7 @@
 #include "staged.h"
 #include "tile.h"
 #include "op.h"
+#include "pipe_kernel.h"
 
 #include <hip/hip_runtime.h>
 
@@ -73,6 +74,15 @@ struct BinDesc {
   int block_base3;
   float* y2b[2];   // three-term launches: y of the second-to-last term of launch L (FP32) in y2b[L & 1]
   int active;     // 0: the bin is advanced by the single-op path instead
+  // pipeline sweeps
+  int ncbp;       // strips of kPipeCols columns
+  int segs;       // segments planned: segment s runs in launch off + s, s < segs
+  int off;
+  int pd;         // degree to expect: p of pd - 1 .. pd + 1 is stored in pred
+  long pbase;     // the bin's partials within a launch parity's
+  double* yb[3];  // segment s reads yb[s mod 3] and writes yb[(s + 1) mod 3],
+  double* pp[3];  // p of its last term in pp[s mod 3]
+  double* pred[3];
 };
 
 struct BinCtl {
@@ -1253,6 +1263,265 @@ __global__ __launch_bounds__(64) void batch_publish_kernel(const BinCtl* __restr
   }
 }
 
+// ---------------------------------------------------------------------------
+// Pipeline sweeps (the default): the pipeline kernel's blocks, each on one run
+// of rows of one strip of one bin.  Segment 0 of a bin's sweep forms the stage
+// vector and terms 1 .. 6, every later segment seven terms.
+//
+// The host plans as many segments per bin as its last degree plus one takes
+// (the bins sorted by them, so that a launch's blocks are a prefix of the block
+// map) and each launch's run length.  A bin that has not stopped by then goes on
+// in launches the host adds after it has read the outcomes.  Each launch's
+// first blocks decide the previous one's segments, a wave per bin.  p is stored
+// at the end of a segment and at the three degrees around the expected one; a
+// bin that stops elsewhere has its last segment replayed up to the stop.
+//
+// 256 bins of 128^2 .. 512^2, FP32 fields: a pass over memory (56 B a point with
+// FP64 fields) then covers seven terms where the three-term blocks took 60 B for
+// three, and stage and first term have no launch of their own: two steps 5727 us
+// before, 3411 us now; 24 bins of odd widths (two terms a launch, a wave per
+// tile) 1138 / 548 us.
+// ---------------------------------------------------------------------------
+__host__ __device__ inline int seg_first(int s) { return s == 0 ? 0 : kPipeMax * s - 1; }  // terms before segment s
+__host__ __device__ inline int seg_of(int m) { return m < kPipeMax ? 0 : (m - (kPipeMax - 1) - 1) / kPipeMax + 1; }
+__host__ __device__ inline int seg_terms(int s, int M) {
+  const int n = seg_first(s + 1) - seg_first(s), left = M - seg_first(s);
+  return n < left ? n : left;
+}
+
+struct PipeBatch {
+  const BinDesc* bins;
+  const int2* map;  // block -> bin and its unit there (strip fastest)
+  BinCtl* ctl;
+  double* partials;
+  long part_stride;
+  int nbins, ndec;  // bins, decision blocks
+  int L;            // launch
+  int rows, prows;  // rows per run in this launch and the one before
+};
+
+// a block's launch (the fields of PipeArgs that the kernel's waves read)
+struct PipeBin {
+  const double* yin;
+  const double* pin;
+  const double* src;
+  double srcc, d0, invg;
+  double* yout;
+  int nst, stage, replay, rows, ncb, nblocks, slot;
+  long slot_stride;
+  double* partials;
+  const BinDesc* B;
+  int k, pd;
+  double* plast;
+  __device__ double shift_of(int t) const { return stage && t == 1 ? 0.0 : uni(B->shift[k + t - 1 - stage]); }
+  __device__ double dk_of(int t) const { return uni(B->d[k + t - stage]); }
+  __device__ double* p_of(int t) const {
+    if (t == nst) return plast;
+    const int i = k + t - stage - (pd - 1);
+    return replay || t <= stage || i < 0 || i > 2 ? nullptr : uni(B->pred[i]);
+  }
+};
+
+// whether p of the bin's stopping degree was stored, and where
+__device__ __forceinline__ const double* pipe_result(const BinDesc& B, const BinCtl& c, bool replayed) {
+  if (replayed) return B.pred[0];
+  if (c.inner == 0) return B.pp[c.launch % 3];
+  const int i = c.degree - (B.pd - 1);
+  return i >= 0 && i <= 2 ? B.pred[i] : nullptr;
+}
+
+// Decision on the bin's segment of launch A.L - 1, if it had one (whole wave,
+// fixed order); the tests are bin_decide's.
+__device__ __forceinline__ void pipe_bin_decide(const PipeBatch& A, int b) {
+  const BinDesc& B = A.bins[b];
+  const int seg = A.L - 1 - B.off;
+  if (!B.active || seg < 0 || seg >= B.segs) return;
+  BinCtl* c = A.ctl + b;
+  if (__hip_atomic_load(&c->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+  const int k = seg_first(seg), n = seg_terms(seg, B.max_degree), lane = threadIdx.x & 63;
+  if (n < 1 || c->degree >= k + n) return;
+  const int nb = B.ncbp * ((B.f.ny + A.prows - 1) / A.prows);
+  const double* part = A.partials + (long)((A.L - 1) & 1) * A.part_stride + B.pbase;
+  double tn[kPipeMax], pn[kPipeMax], m0 = 0.0;
+#pragma unroll
+  for (int t = 0; t < kPipeMax; ++t) {
+    tn[t] = pn[t] = 0.0;
+    if (t >= n) continue;
+    for (int i = lane; i < nb; i += 64) {
+      tn[t] += part[3L * t * nb + i];
+      pn[t] += part[(3L * t + 1) * nb + i];
+    }
+  }
+  for (int i = lane; i < nb; i += 64) m0 = nanmax(m0, part[2L * nb + i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+    for (int t = 0; t < kPipeMax; ++t) {
+      tn[t] += __shfl_xor(tn[t], o);
+      pn[t] += __shfl_xor(pn[t], o);
+    }
+    m0 = nanmax(m0, __shfl_xor(m0, o));
+  }
+  double hist[kStopHist];
+#pragma unroll
+  for (int i = 0; i < kStopHist; ++i) hist[i] = c->hist[i];
+  int stop = 0, status = 0, degree = 0;
+  double tn2 = 0.0, pn2 = 0.0;
+#pragma unroll
+  for (int t = 0; t < kPipeMax; ++t) {
+    if (t >= n || stop) continue;
+    tn2 = tn[t];
+    pn2 = pn[t];
+    degree = k + t + 1;
+    if (!isfinite(tn2) || !isfinite(pn2)) {
+      stop = 1; status = 2;
+    } else if (degree == 1 && m0 == 0.0) {
+      stop = 1; status = 1; degree = 0;
+    } else if (window_stop(hist, degree, sqrt(tn2), pn2, B.tol)) {
+      stop = 1; status = 1;
+    } else if (degree >= B.max_degree) {
+      stop = 1; status = 3;
+    }
+  }
+  if (lane != 0) return;
+  c->tn2 = tn2;
+  c->pn2 = pn2;
+#pragma unroll
+  for (int i = 0; i < kStopHist; ++i) c->hist[i] = hist[i];
+  c->degree = degree;
+  c->status = status;
+  if (stop) {
+    c->inner = degree > 0 ? k + n - degree : 0;
+    c->launch = seg;
+  }
+  __hip_atomic_store(&c->stop, stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A launch of segments (MODE PIPE_LATER: segments 1 and on, else segment 0);
+// REPLAY: the stopped bins' last segments up to the stopping term, p to pred[0].
+template <typename TF, bool ADVF, bool PAIR, bool NT, int MODE, bool REPLAY>
+__global__ __launch_bounds__(kPipeThreads, ADVF ? 2 : 4) void batch_pipe_kernel(PipeBatch A) {
+  extern __shared__ __attribute__((aligned(16))) double lds[];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if ((int)blockIdx.x < A.ndec) {
+    const int b = (int)blockIdx.x * (1 + kPipeMax) + wave;
+    if (b >= A.nbins) return;
+    if constexpr (MODE != PIPE_LATER) {
+      // a new sweep (no block of this launch reads the control blocks)
+      if ((threadIdx.x & 63) == 0) {
+        BinCtl c{};
+        c.launch = kNoLaunch;
+        A.ctl[b] = c;
+      }
+    } else if constexpr (!REPLAY) {
+      pipe_bin_decide(A, b);
+    }
+    return;
+  }
+  const int2 e = A.map[(int)blockIdx.x - A.ndec];
+  const int b = __builtin_amdgcn_readfirstlane(e.x), unit = __builtin_amdgcn_readfirstlane(e.y);
+  const BinDesc& B = A.bins[b];
+  if (!uni(B.active)) return;
+  const int seg = REPLAY ? uni(A.ctl[b].launch) : A.L - uni(B.off);
+  const int k = seg_first(seg);
+  int n = seg_terms(seg, uni(B.max_degree));
+  if (REPLAY) n -= uni(A.ctl[b].inner);
+  if (n < 1 || (!REPLAY && seg >= uni(B.segs))) return;
+  if constexpr (MODE == PIPE_LATER && !REPLAY) {
+    // one read of the stop flag for the whole block (as in pipe_kernel)
+    int* flag = reinterpret_cast<int*>(lds);
+    if (threadIdx.x == 0) *flag = __hip_atomic_load(&A.ctl[b].stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int stop = __builtin_amdgcn_readfirstlane(*flag);
+    if (stop) return;
+    __syncthreads();
+  }
+  FieldView F = B.f;
+  F.kxx = uni(F.kxx);
+  F.kxy = uni(F.kxy);
+  F.kyy = uni(F.kyy);
+  F.ax = uni(F.ax);
+  F.ay = uni(F.ay);
+  F.nx = uni(F.nx);
+  F.ny = uni(F.ny);
+  F.bc = uni(F.bc);
+  F.axc = uni(F.axc);
+  F.ayc = uni(F.ayc);
+  PipeBin P;
+  P.stage = MODE == PIPE_LATER ? 0 : 1;
+  P.nst = n + P.stage;
+  P.replay = REPLAY;
+  P.yin = MODE == PIPE_LATER ? uni(B.yb[seg % 3]) : uni(B.u);
+  P.pin = MODE == PIPE_LATER ? uni(B.pp[(seg + 2) % 3]) : nullptr;
+  P.src = (MODE & PIPE_SRC) ? uni(B.S) : nullptr;
+  P.srcc = 0.0;
+  P.d0 = 0.0;  // (the stage vector w enters p as d_0 w)
+  P.invg = uni(B.invg);
+  P.yout = REPLAY ? nullptr : uni(B.yb[(seg + 1) % 3]);
+  P.plast = REPLAY ? uni(B.pred[0]) : uni(B.pp[seg % 3]);
+  P.B = &B;
+  P.k = k;
+  P.pd = uni(B.pd);
+  P.rows = A.rows;
+  P.ncb = uni(B.ncbp);
+  P.nblocks = P.ncb * ((F.ny + A.rows - 1) / A.rows);
+  P.slot = 0;
+  P.slot_stride = 0;
+  P.partials = uni(A.partials + (long)(A.L & 1) * A.part_stride + B.pbase);
+  const PipeRun r = pipe_run(F, P, unit);
+  if (wave == 0) {
+    pipe_loader<TF, double, ADVF, PAIR, NT, MODE>(F, P, lds, r);
+  } else if (MODE != PIPE_LATER && wave == 1) {
+    pipe_stage<double, ADVF, PAIR, NT, MODE>(F, P, lds, r, 1, unit);
+  } else if (wave <= P.nst) {
+    pipe_stage<double, ADVF, PAIR, NT, PIPE_LATER>(F, P, lds, r, wave, unit);
+  } else {
+    for (int t = 0; t < r.nticks; ++t) __syncthreads();
+  }
+}
+
+// decision on the last launch's segments: one wave per bin
+__global__ __launch_bounds__(64) void batch_pipe_finalize_kernel(PipeBatch A) { pipe_bin_decide(A, blockIdx.x); }
+
+// u_b += dt p_b of the converged bins not advanced yet whose p was stored, or
+// (replayed) of those that have it from a replay; one wave per tile.
+template <int VEC>
+__global__ __launch_bounds__(64 * kBWaves) void batch_pipe_update_kernel(BatchArgs A, double* const* u, int replayed) {
+  const int gt = wave_unit();
+  if (gt >= A.total_tiles) return;
+  const int b = __builtin_amdgcn_readfirstlane(A.tile_bin[gt]);
+  const BinDesc& B = A.bins[b];
+  const BinCtl& c = A.ctl[b];
+  if (!B.active || c.status != 1 || c.degree == 0) return;  // degree 0: p = 0
+  const bool stored = pipe_result(B, c, false) != nullptr;
+  if (replayed ? stored : (c.upd || !stored)) return;
+  const double* __restrict__ pb = pipe_result(B, c, replayed);
+  double* __restrict__ ub = u[b];
+  const int t = gt - B.tile_base, nx = B.f.nx;
+  const int rb = t / B.ncb, cb = t - rb * B.ncb;
+  const int j0 = rb * B.rows, j1 = min(j0 + B.rows, B.f.ny);
+  const int col0 = cb * kWave * VEC + (int)(threadIdx.x & 63) * VEC;
+  if (col0 >= nx) return;
+  const double dt = B.dt;
+  constexpr int G = 8;
+  for (int j = j0; j < j1; j += G) {
+    double uu[G][VEC], pp[G][VEC];
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const long ro = (long)min(j + q, j1 - 1) * nx;
+      ldr<double, VEC>(ub + ro, col0, uu[q]);
+      ldr<double, VEC>(pb + ro, col0, pp[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      if (j + q >= j1) break;
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) uu[q][v] = uu[q][v] + dt * pp[q][v];
+      str<double, VEC>(ub + (long)(j + q) * nx, col0, uu[q]);
+    }
+  }
+}
+
 }  // namespace adl
 
 using namespace adl;
@@ -1293,6 +1562,16 @@ struct adl_batch {
   long part_stride = 0;  // doubles per launch parity of the partials
   int two = 1;           // two Newton terms per launch after the first
   int three = 0;         // three (LDS-staged blocks; all bins two columns per lane)
+  int pipe = 0;          // pipeline sweeps (the default; eager steps only)
+  struct PipeLaunch {
+    int rows, map0, blocks;
+  };
+  std::vector<int2> pmap;             // the launches' block maps
+  std::vector<PipeLaunch> plaunch;    // the planned launches
+  bool pdirty = true;                 // plan again before the next step
+  int2* d_pmap = nullptr;
+  int pL = 0;                         // launches of the sweep so far
+  int pair = 0, stream = 0, src = 0;  // rows readable in pairs; non-temporal hints; a bin has a source
   std::vector<BinDesc> bins;
   std::vector<int> tile_bin, tile_bin2, block_bin3;
   std::vector<double> order_key;  // |alpha| dt of each bin's plan (three-term block order)
@@ -1330,11 +1609,30 @@ int tiles2_of(int nx, int ny, int vec, int rows) {
   return ncb * nrb;
 }
 
+// What pipeline sweeps need beside the tiles: block map entries (run lengths
+// kRunMin, 2 kRunMin .. 4096 at most once each, and a replay's), and partials of
+// a launch with the shortest runs.
+constexpr int kRunMin = 16, kRunMax = 4096, kReplayRows = 64;
+struct PipeRoom {
+  long units, partials;
+};
+int strips_of(const adl_op* op) { return (op->nx + kPipeCols - 1) / kPipeCols; }
+PipeRoom pipe_room(int nbins, adl_op* const* ops) {
+  PipeRoom r{0, 0};
+  for (int b = 0; b < nbins; ++b) {
+    const long ncb = strips_of(ops[b]), ny = ops[b]->ny, most = (ny + kRunMin - 1) / kRunMin;
+    for (int run = kRunMin; run <= kRunMax; run *= 2) r.units += ncb * ((ny + run - 1) / run);
+    r.units += ncb * most;
+    r.partials += 3L * kPipeMax * ncb * most;
+  }
+  return r;
+}
+
 struct BLayout {
-  size_t bins, ctl, tile_bin, tile_bin2, block_bin3, partials, plans, uptrs, seq, total;
+  size_t bins, ctl, tile_bin, tile_bin2, block_bin3, pmap, partials, plans, uptrs, seq, total;
 };
 
-BLayout blayout(int nbins, long max_tiles, int M) {
+BLayout blayout(int nbins, long max_tiles, const PipeRoom& room, int M) {
   BLayout L{};
   size_t o = 0;
   auto take = [&](size_t n) {
@@ -1347,7 +1645,8 @@ BLayout blayout(int nbins, long max_tiles, int M) {
   L.tile_bin = take(sizeof(int) * max_tiles);
   L.tile_bin2 = take(sizeof(int) * max_tiles);
   L.block_bin3 = take(sizeof(int) * max_tiles);
-  L.partials = take(sizeof(double) * 2 * 6 * max_tiles);
+  L.pmap = take(sizeof(int2) * room.units);
+  L.partials = take(sizeof(double) * 2 * std::max(6 * max_tiles, room.partials));
   L.plans = take(sizeof(double) * 2 * (size_t)M * nbins);
   L.uptrs = take(sizeof(double*) * nbins);
   L.seq = take(256);
@@ -1395,6 +1694,7 @@ void build_tiles(adl_batch* B) {
   B->tile_bin2.clear();
   B->block_bin3.clear();
   int base = 0, base2 = 0;
+  long pbase = 0;
   for (int b = 0; b < B->nbins; ++b) {
     adl_op* op = B->ops[b];
     BinDesc& d = B->bins[b];
@@ -1410,6 +1710,9 @@ void build_tiles(adl_batch* B) {
     for (int t = 0; t < d.ntiles2; ++t) B->tile_bin2.push_back(b);
     base += d.ntiles;
     base2 += d.ntiles2;
+    d.ncbp = strips_of(op);
+    d.pbase = pbase;
+    pbase += 3L * kPipeMax * d.ncbp * ((op->ny + kRunMin - 1) / kRunMin);
     // three-term blocks (two columns per lane only): runs of `rows` bands
     // of four rows, i.e. a tile height of 16 rows gives runs of 64 rows
     if (B->vec == 2) {
@@ -1537,6 +1840,15 @@ int enqueue_sweep(adl_batch* B, int k0, int nterms, bool with_stage, hipStream_t
   return ADL_OK;
 }
 
+// the bins' outcomes to the host mirror
+int enqueue_publish(adl_batch* B, hipStream_t st) {
+  hipLaunchKernelGGL(batch_publish_kernel, dim3(1), dim3(64), 0, st, B->d_ctl,
+                     reinterpret_cast<BinCtl*>(B->hmir_dev + 64), B->nbins, B->d_seq,
+                     reinterpret_cast<int*>(B->hmir_dev));
+  BCHK(hipGetLastError());
+  return ADL_OK;
+}
+
 // After a sweep's launches: u_b += dt p_b for the bins converged and not yet
 // advanced, then the outcomes published to the host mirror.
 int enqueue_tail(adl_batch* B, hipStream_t st) {
@@ -1548,11 +1860,8 @@ int enqueue_tail(adl_batch* B, hipStream_t st) {
   else
     hipLaunchKernelGGL((batch_update_kernel<1>), dim3(blocks_for(B->total_tiles)), dim3(64 * kBWaves), 0, st, a,
                        B->d_uptrs);
-  hipLaunchKernelGGL(batch_publish_kernel, dim3(1), dim3(64), 0, st, B->d_ctl,
-                     reinterpret_cast<BinCtl*>(B->hmir_dev + 64), B->nbins, B->d_seq,
-                     reinterpret_cast<int*>(B->hmir_dev));
   BCHK(hipGetLastError());
-  return ADL_OK;
+  return enqueue_publish(B, st);
 }
 
 // Waits until publication number `want` has reached the host mirror (the
@@ -1575,8 +1884,97 @@ int await_publication(adl_batch* B, int want, hipStream_t st) {
   return ADL_OK;
 }
 
-int upload_bins(adl_batch* B, double* const* u, const double* const* S, double dt, double tol, hipStream_t st,
-                bool& changed) {
+// Plans a pipeline sweep: segs (host and device) per bin, then the launches
+// from `L0` on with their run lengths and the block maps.  Run lengths are powers
+// of two; a launch takes the one with the least work per slot plus longest
+// block, blocks of r rows lasting r + 3 kPipeMax ticks (two blocks a CU, with
+// advection fields one).
+void plan_launches(adl_batch* B, int L0, const std::vector<int>& bins) {
+  std::vector<int> ord(bins);
+  std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) {
+    const int ea = B->bins[a].off + B->bins[a].segs, eb = B->bins[b].off + B->bins[b].segs;
+    return ea != eb ? ea > eb : B->order_key[a] > B->order_key[b];
+  });
+  B->pmap.clear();
+  B->plaunch.clear();
+  std::map<int, int> at;  // rows -> start of its map
+  const int slots = B->advf ? 256 : 512;
+  auto units = [&](int b, int r) { return (long)B->bins[b].ncbp * ((B->ops[b]->ny + r - 1) / r); };
+  for (int L = L0;; ++L) {
+    size_t n = 0;
+    while (n < ord.size() && B->bins[ord[n]].off + B->bins[ord[n]].segs > L) ++n;
+    if (n == 0) break;
+    int best = kRunMin;
+    double cost = INFINITY;
+    for (int r = kRunMin; r <= kRunMax; r *= 2) {
+      double work = 0.0;
+      int longest = 0;
+      for (size_t i = 0; i < n; ++i) {
+        const int ny = B->ops[ord[i]]->ny, len = std::min(r, ny);
+        const long whole = ny / len, ncb = B->bins[ord[i]].ncbp;
+        work += (double)ncb * (whole * (len + 3 * kPipeMax) + (ny % len ? ny % len + 3 * kPipeMax : 0));
+        longest = std::max(longest, len);
+      }
+      const double c = work / slots + longest + 3 * kPipeMax;
+      if (c < cost) {
+        cost = c;
+        best = r;
+      }
+    }
+    if (!at.count(best)) {
+      at[best] = (int)B->pmap.size();
+      for (int b : ord)
+        for (long t = 0; t < units(b, best); ++t) B->pmap.push_back(make_int2(b, (int)t));
+    }
+    long blocks = 0;
+    for (size_t i = 0; i < n; ++i) blocks += units(ord[i], best);
+    B->plaunch.push_back({best, at[best], (int)blocks});
+  }
+}
+
+// The segments each active bin's next sweep should take, and the degree to
+// expect: the last degree plus one (the first sweep: a guess).
+void pipe_expect(adl_batch* B, int b, double dt, int& segs, int& pd) {
+  adl_op* op = B->ops[b];
+  Plan& P = get_plan(op, 1, op->alpha, dt);
+  const int M = B->bins[b].max_degree;
+  pd = P.last_degree > 0 ? P.last_degree : (int)(3.5 * std::sqrt(std::fabs(op->alpha) * dt) + 4.0);
+  pd = std::max(1, std::min(pd, M));
+  segs = seg_of(std::min(pd + 1, M)) + 1;
+}
+
+// Plans the next step's sweep if the last plan does not serve: a bin needs
+// more segments, or an eighth of the segments or of the expected degrees are
+// off.  Returns whether the bins changed.
+bool pipe_plan(adl_batch* B, double dt) {
+  bool redo = B->pdirty;
+  int total = 0, waste = 0, off = 0, act = 0;
+  std::vector<int> segs(B->nbins, 0), pd(B->nbins, 0), bins;
+  for (int b = 0; b < B->nbins; ++b) {
+    const BinDesc& d = B->bins[b];
+    if (!d.active) continue;
+    pipe_expect(B, b, dt, segs[b], pd[b]);
+    bins.push_back(b);
+    redo |= segs[b] > d.segs;
+    total += d.segs;
+    waste += std::max(0, d.segs - segs[b]);
+    off += std::abs(pd[b] - d.pd) > 1;
+    ++act;
+  }
+  redo |= 8 * waste > total || 8 * off > act;
+  if (!redo) return false;
+  for (int b : bins) {
+    B->bins[b].segs = segs[b];
+    B->bins[b].off = 0;
+    B->bins[b].pd = pd[b];
+  }
+  plan_launches(B, 0, bins);
+  B->pdirty = false;
+  return true;
+}
+
+int upload_bins(adl_batch* B, double* const* u, const double* const* S, double dt, double tol, bool pipe,
+                hipStream_t st, bool& changed) {
   changed = false;
   const int M = B->max_degree + 1;
   std::vector<double> planbuf;
@@ -1602,6 +2000,15 @@ int upload_bins(adl_batch* B, double* const* u, const double* const* S, double d
     // the second-to-last term of each launch
     d.y2b[0] = reinterpret_cast<float*>(op->p3);
     d.y2b[1] = reinterpret_cast<float*>(op->p4);
+    d.yb[0] = reinterpret_cast<double*>(op->ybuf[0]);
+    d.yb[1] = reinterpret_cast<double*>(op->ybuf[1]);
+    d.yb[2] = op->w1;
+    d.pp[0] = op->p;
+    d.pp[1] = op->p2;
+    d.pp[2] = op->p3;
+    d.pred[0] = op->p4;
+    d.pred[1] = op->tmp;
+    d.pred[2] = op->tmp2;
     d.tol = tol;
     d.dt = dt;
     d.max_degree = std::min(op->max_degree, B->max_degree);
@@ -1629,6 +2036,30 @@ int upload_bins(adl_batch* B, double* const* u, const double* const* S, double d
     if (B->total_blocks3 > 0)
       BCHK(hipMemcpy(B->d_block_bin3, B->block_bin3.data(), sizeof(int) * B->total_blocks3, hipMemcpyHostToDevice));
   }
+  if (pipe) {
+    if (changed || plans_changed) {
+      bool even = true;
+      int src = 0;
+      double bytes = 0.0;
+      for (int b = 0; b < B->nbins; ++b) {
+        const BinDesc& d = B->bins[b];
+        even &= d.f.nx % 2 == 0 && !(reinterpret_cast<uintptr_t>(d.u) & 15) && !(reinterpret_cast<uintptr_t>(d.S) & 15);
+        src |= d.S != nullptr;
+        // (fields, u, S, three y and p each)
+        bytes += ((B->advf ? 5.0 : 3.0) * (B->f32 ? 4.0 : 8.0) + 64.0) * d.f.nx * d.f.ny;
+      }
+      B->pair = even;
+      B->src = src;
+      B->stream = bytes > kStreamMinBytes;
+      B->pdirty = true;
+    }
+    if (pipe_plan(B, dt)) {
+      if (!changed && !plans_changed) BCHK(hipStreamSynchronize(st));
+      plans_changed = true;
+      if (!B->pmap.empty())
+        BCHK(hipMemcpy(B->d_pmap, B->pmap.data(), sizeof(int2) * B->pmap.size(), hipMemcpyHostToDevice));
+    }
+  }
   if (changed || plans_changed) {
     BCHK(hipStreamSynchronize(st));
     BCHK(hipMemcpy(B->d_bins, B->bins.data(), sizeof(BinDesc) * B->nbins, hipMemcpyHostToDevice));
@@ -1638,6 +2069,132 @@ int upload_bins(adl_batch* B, double* const* u, const double* const* S, double d
   }
   (void)st;
   return ADL_OK;
+}
+
+template <typename TF, bool ADVF, bool PAIR, bool NT, int MODE, bool REPLAY>
+void pipe_launch(const adl_batch* B, const PipeBatch& a, int blocks, hipStream_t st) {
+  const size_t lds = pipe_lds_bytes(kPipeMax, ADVF, (MODE & PIPE_SRC) != 0);
+  hipLaunchKernelGGL((batch_pipe_kernel<TF, ADVF, PAIR, NT, MODE, REPLAY>), dim3(a.ndec + blocks), dim3(kPipeThreads),
+                     lds, st, a);
+}
+template <typename TF, bool ADVF, int MODE, bool REPLAY>
+void pipe_vectors(const adl_batch* B, const PipeBatch& a, int blocks, hipStream_t st) {
+  if (!B->pair) pipe_launch<TF, ADVF, false, false, MODE, REPLAY>(B, a, blocks, st);
+  else if (B->stream) pipe_launch<TF, ADVF, true, true, MODE, REPLAY>(B, a, blocks, st);
+  else pipe_launch<TF, ADVF, true, false, MODE, REPLAY>(B, a, blocks, st);
+}
+template <typename TF, bool ADVF, bool REPLAY>
+void pipe_mode(const adl_batch* B, const PipeBatch& a, bool first, int blocks, hipStream_t st) {
+  if (!first) pipe_vectors<TF, ADVF, PIPE_LATER, REPLAY>(B, a, blocks, st);
+  else if (B->src) pipe_vectors<TF, ADVF, PIPE_FIRST | PIPE_STAGE | PIPE_SRC, REPLAY>(B, a, blocks, st);
+  else pipe_vectors<TF, ADVF, PIPE_FIRST | PIPE_STAGE, REPLAY>(B, a, blocks, st);
+}
+template <bool REPLAY>
+void pipe_fields(const adl_batch* B, const PipeBatch& a, bool first, int blocks, hipStream_t st) {
+  if (B->f32) {
+    if (B->advf) pipe_mode<float, true, REPLAY>(B, a, first, blocks, st);
+    else pipe_mode<float, false, REPLAY>(B, a, first, blocks, st);
+  } else {
+    if (B->advf) pipe_mode<double, true, REPLAY>(B, a, first, blocks, st);
+    else pipe_mode<double, false, REPLAY>(B, a, first, blocks, st);
+  }
+}
+
+PipeBatch pipe_args(const adl_batch* B) {
+  PipeBatch a{};
+  a.bins = B->d_bins;
+  a.ctl = B->d_ctl;
+  a.partials = B->d_partials;
+  a.part_stride = B->part_stride;
+  a.nbins = B->nbins;
+  return a;
+}
+
+// The planned launches (from launch L0 on; L0 = 0: a new sweep), then the
+// decision on the last one.
+int enqueue_pipe(adl_batch* B, int L0, hipStream_t st) {
+  PipeBatch a = pipe_args(B);
+  a.ndec = (B->nbins + kPipeMax) / (1 + kPipeMax);
+  // (the launch before L0 is decided already: the first decisions below find
+  // its segments' degrees taken)
+  a.prows = kRunMin;
+  B->pL = L0;
+  for (const adl_batch::PipeLaunch& l : B->plaunch) {
+    a.L = B->pL++;
+    a.rows = l.rows;
+    a.map = B->d_pmap + l.map0;
+    pipe_fields<false>(B, a, a.L == 0, l.blocks, st);
+    a.prows = l.rows;
+  }
+  a.L = B->pL;
+  hipLaunchKernelGGL(batch_pipe_finalize_kernel, dim3(B->nbins), dim3(64), 0, st, a);
+  BCHK(hipGetLastError());
+  return ADL_OK;
+}
+
+int enqueue_pipe_update(adl_batch* B, bool replayed, hipStream_t st) {
+  const BatchArgs a = base_args(B);
+  const dim3 grid(blocks_for(B->total_tiles)), blk(64 * kBWaves);
+  if (B->vec == 2) hipLaunchKernelGGL((batch_pipe_update_kernel<2>), grid, blk, 0, st, a, B->d_uptrs, (int)replayed);
+  else hipLaunchKernelGGL((batch_pipe_update_kernel<1>), grid, blk, 0, st, a, B->d_uptrs, (int)replayed);
+  BCHK(hipGetLastError());
+  return ADL_OK;
+}
+
+// One step's pipeline sweep: the planned launches, u advanced where p is
+// stored, the outcomes read; bins still running go on (segments of a bin are
+// launched one after the other, so a bin's offset grows by the launches it sat
+// out), and bins that stopped between stored degrees are replayed.
+int pipe_step(adl_batch* B, hipStream_t st) {
+  int rc = enqueue_pipe(B, 0, st);
+  while (true) {
+    if (rc == ADL_OK) rc = enqueue_pipe_update(B, false, st);
+    if (rc == ADL_OK) rc = enqueue_publish(B, st);
+    if (rc != ADL_OK) return rc;
+    ++B->pubs;
+    rc = await_publication(B, B->pubs, st);
+    if (rc != ADL_OK) return rc;
+    std::vector<int> run;
+    for (int b = 0; b < B->nbins; ++b) {
+      BinDesc& d = B->bins[b];
+      if (!d.active || B->h_ctl[b].stop) continue;
+      d.off = B->pL - d.segs;
+      d.segs = std::min(seg_of(d.max_degree) + 1, d.segs + std::max(1, d.segs / 4));
+      run.push_back(b);
+    }
+    if (run.empty()) break;
+    hipLaunchKernelGGL(batch_mark_kernel, dim3((B->nbins + 255) / 256), dim3(256), 0, st, B->d_ctl, B->nbins);
+    plan_launches(B, B->pL, run);
+    B->pdirty = true;
+    BCHK(hipStreamSynchronize(st));
+    BCHK(hipMemcpy(B->d_bins, B->bins.data(), sizeof(BinDesc) * B->nbins, hipMemcpyHostToDevice));
+    BCHK(hipMemcpy(B->d_pmap, B->pmap.data(), sizeof(int2) * B->pmap.size(), hipMemcpyHostToDevice));
+    rc = enqueue_pipe(B, B->pL, st);
+  }
+  // replays: segment 0 and later ones (their blocks behind the launches' maps)
+  std::vector<int2> map;
+  int first = 0;
+  for (int later = 0; later < 2; ++later) {
+    for (int b = 0; b < B->nbins; ++b) {
+      const BinDesc& d = B->bins[b];
+      const BinCtl& c = B->h_ctl[b];
+      if (!d.active || c.status != 1 || c.degree == 0 || c.inner == 0 || std::abs(c.degree - d.pd) <= 1) continue;
+      if ((c.launch > 0) != (later == 1)) continue;
+      const int n = d.ncbp * ((B->ops[b]->ny + kReplayRows - 1) / kReplayRows);
+      for (int t = 0; t < n; ++t) map.push_back(make_int2(b, t));
+    }
+    if (!later) first = (int)map.size();
+  }
+  if (map.empty()) return ADL_OK;
+  int2* at = B->d_pmap + B->pmap.size();
+  BCHK(hipMemcpy(at, map.data(), sizeof(int2) * map.size(), hipMemcpyHostToDevice));
+  PipeBatch a = pipe_args(B);
+  a.rows = a.prows = kReplayRows;
+  a.map = at;
+  if (first > 0) pipe_fields<true>(B, a, true, first, st);
+  a.map = at + first;
+  if ((int)map.size() > first) pipe_fields<true>(B, a, false, (int)map.size() - first, st);
+  return enqueue_pipe_update(B, true, st);
 }
 
 // Autotune results of this process, by tuning key.
@@ -1664,7 +2221,7 @@ int autotune_key(const adl_batch* B, const int* candidates, int ncand, std::stri
   std::sort(shapes.begin(), shapes.end());
   key = std::string(prop.gcnArchName) + "|f32=" + std::to_string(B->f32) + "|adv=" + std::to_string((int)B->advf) +
         "|vec=" + std::to_string(B->vec) + "|two=" + std::to_string(B->two) +
-        "|three=" + std::to_string(B->three) + "|cand=";
+        "|three=" + std::to_string(B->three) + "|pipe=" + std::to_string(B->pipe) + "|cand=";
   for (int c = 0; c < ncand; ++c) key += std::to_string(candidates[c]) + ",";
   key += "|bins=";
   for (const auto& sh : shapes) key += std::to_string(sh.first) + "x" + std::to_string(sh.second) + ",";
@@ -1692,7 +2249,7 @@ size_t adl_batch_workspace_bytes(int nbins, adl_op* const* ops, int max_degree) 
   for (int b = 0; b < nbins; ++b)
     if (!ops[b]) return 0;
   const int M = (max_degree > 0 ? max_degree : kMaxDegreeDefault) + 1;
-  return blayout(nbins, max_tiles_for(nbins, ops), M).total;
+  return blayout(nbins, max_tiles_for(nbins, ops), pipe_room(nbins, ops), M).total;
 }
 
 int adl_batch_create(int nbins, adl_op* const* ops, void* workspace, size_t ws_bytes, int tile_rows,
@@ -1717,7 +2274,8 @@ int adl_batch_create(int nbins, adl_op* const* ops, void* workspace, size_t ws_b
   if (tile_rows < 0) return bfail(ADL_EINVAL, "tile_rows must be >= 0");
   const int M = kMaxDegreeDefault + 1;
   const long mt = max_tiles_for(nbins, ops);
-  const BLayout L = blayout(nbins, mt, M);
+  const PipeRoom room = pipe_room(nbins, ops);
+  const BLayout L = blayout(nbins, mt, room, M);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255)) return bfail(ADL_ENOWORKSPACE, "workspace missing or not 256-byte aligned");
   if (ws_bytes < L.total) return bfail(ADL_ENOWORKSPACE, "batch workspace too small");
   adl_batch* B = new (std::nothrow) adl_batch();
@@ -1738,7 +2296,9 @@ int adl_batch_create(int nbins, adl_op* const* ops, void* workspace, size_t ws_b
   B->d_tile_bin = reinterpret_cast<int*>(B->ws + L.tile_bin);
   B->d_tile_bin2 = reinterpret_cast<int*>(B->ws + L.tile_bin2);
   B->d_block_bin3 = reinterpret_cast<int*>(B->ws + L.block_bin3);
-  B->part_stride = 6 * mt;
+  B->part_stride = std::max(6 * mt, room.partials);
+  B->d_pmap = reinterpret_cast<int2*>(B->ws + L.pmap);
+  B->pipe = 1;
   B->d_partials = reinterpret_cast<double*>(B->ws + L.partials);
   B->d_plans = reinterpret_cast<double*>(B->ws + L.plans);
   B->d_uptrs = reinterpret_cast<double**>(B->ws + L.uptrs);
@@ -1811,7 +2371,8 @@ int adl_batch_set_term_fusion(adl_batch* B, int mode) {
   if (mode == 3 && B->vec != 2)
     return bfail(ADL_EINVAL, "three terms per launch need every bin at two columns per lane (nx even, >= 128)");
   const int two = mode != 0, three = mode == 3;
-  if (two == B->two && three == B->three) return ADL_OK;
+  if (two == B->two && three == B->three && !B->pipe) return ADL_OK;
+  B->pipe = 0;
   B->two = two;
   B->three = three;
   BCHK(hipStreamSynchronize(B->cap_stream));
@@ -1867,13 +2428,13 @@ int adl_batch_autotune(adl_batch* B, double* const* u, const double* const* S_ha
     int rc = adl_batch_set_tile_rows(B, candidates[c]);
     if (rc != ADL_OK) return rc;
     bool changed;
-    rc = upload_bins(B, u, S_half, dt, tol, st, changed);
+    rc = upload_bins(B, u, S_half, dt, tol, B->pipe, st, changed);
     if (rc != ADL_OK) return rc;
     const int nterms = predicted_terms(B, dt);
     float ms_min = INFINITY;
     for (int rep = 0; rep < 3; ++rep) {
       BCHK(hipEventRecord(e0, st));
-      rc = enqueue_sweep(B, 0, nterms, true, st, nullptr, false);
+      rc = B->pipe ? enqueue_pipe(B, 0, st) : enqueue_sweep(B, 0, nterms, true, st, nullptr, false);
       if (rc != ADL_OK) return rc;
       BCHK(hipEventRecord(e1, st));
       BCHK(hipEventSynchronize(e1));
@@ -1913,13 +2474,17 @@ int adl_batch_midpoint_step(adl_batch* B, double* const* u, const double* const*
   }
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   bool changed;
-  int rc = upload_bins(B, u, S_half, dt, tol, st, changed);
+  const bool pipe = B->pipe && !use_graph;
+  int rc = upload_bins(B, u, S_half, dt, tol, pipe, st, changed);
   if (rc != ADL_OK) return rc;
   const int nterms = predicted_terms(B, dt);
   bool any_active = false;
   for (int b = 0; b < B->nbins; ++b) any_active |= B->bins[b].active != 0;
 
-  if (any_active) {
+  if (any_active && pipe) {
+    rc = pipe_step(B, st);
+    if (rc != ADL_OK) return rc;
+  } else if (any_active) {
     if (use_graph) {
       const bool rebuild = !B->gexec || changed || nterms > B->g_launches || B->g_rows != B->rows;
       if (rebuild) {

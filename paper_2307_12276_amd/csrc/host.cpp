@@ -407,7 +407,6 @@ static double leja_bytes(const adl_op* op, int k, bool with_w2) {
 // lines the next launch would find in cache (measured on MI355X: 10 % slower
 // launches at 512^2 and at 2048^2, 335 MB; 4-10 % faster at 2896^2 and
 // 4096^2).
-constexpr double kStreamMinBytes = 512.0 * 1024 * 1024;
 static int streaming_on(const adl_op* op) {
   if (op->streaming >= 0) return op->streaming;
   const double fs = op->f.f32 ? 4.0 : 8.0;

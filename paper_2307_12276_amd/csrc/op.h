@@ -12,6 +12,7 @@ namespace adl {
 
 constexpr int kMaxDegreeDefault = 500;
 constexpr double kRhoMaxDefault = 1600.0;
+constexpr double kStreamMinBytes = 512.0 * 1024 * 1024;  // working sets beyond this are streamed (streaming_on)
 constexpr int kMaxDoublings = 6;
 
 struct Plan {
