@@ -195,7 +195,7 @@ void build_plan(Plan& P, int l, double alpha, double h, int M) {
     if (k + 1 < M) P.s[k + 1] = (2.0 - xi[k]) * P.s[k];
   }
   P.invg = 1.0 / gamma;
-  P.last_degree = -1;
+  P.last_degree = P.prev_degree = -1;
 }
 
 }  // namespace adl
@@ -271,6 +271,8 @@ static const Tiling& tiling_for(const adl_op* op, const void* a, const void* b =
 struct SweepOut {
   int degree = 0;
   int status = 0;  // 1 converged, 2 non-finite, 3 degree cap
+  bool anywhere = false;      // in: the result may be left in a workspace vector ...
+  const double* p = nullptr;  // out: ... this one (else in the sweep's p_out)
 };
 
 static int read_ctl(adl_op* op, hipStream_t st) {
@@ -501,10 +503,11 @@ static bool stage_fusable(const adl_op* op, const double* u, const double* s, do
 // its terms.
 //
 // Chunks: the first one covers the plan's last degree (the first sweep of a
-// plan: a guess from rho h) in whole launches, and the launch that holds the
-// predicted degree stores p of that term too (into p_out; 8 B per point more
-// on one launch), so that a sweep stopping there needs no replay and one
-// stopping a little later no further chunk.
+// plan: a guess from rho h) in whole launches.  p is also stored at the plan's
+// last degree and at the one before it, where they are not a launch's last
+// term (8 B per point more on one launch each; a sequence of steps alternates
+// between neighbouring degrees as a rule), so that a sweep stopping there needs
+// no replay (175 us at 4096^2) and one stopping a little later no further chunk.
 static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, double w2scale, double* p_out,
                       double tol, int maxdeg, hipStream_t st, SweepOut& out, const double* stage_u,
                       const double* stage_s) {
@@ -516,21 +519,28 @@ static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, do
       std::max(1, std::min(maxdeg, known ? P.last_degree : (int)(3.5 * std::sqrt(std::fabs(P.alpha) * P.h) + 4.0)));
   // buffers: launch L reads y from ybuf[L mod 3] and p from pbuf[(L + 2) mod 3]
   // and writes y to ybuf[(L + 1) mod 3], p to pbuf[L mod 3]
-  double* ws[5] = {op->p, op->p2, op->p3, op->p4, op->tmp2};
-  int wi = 0;
-  auto take_ws = [&]() {
-    while (ws[wi] == p_out || ws[wi] == v || ws[wi] == w2) ++wi;
-    return ws[wi++];
-  };
+  // (workspace vectors that hold neither the caller's vectors nor its results)
+  std::vector<double*> ws;
+  for (double* q : {op->p, op->p2, op->p3, op->p4, op->tmp, op->tmp2})
+    if (q != p_out && q != v && q != w2 && !(q == op->tmp2 && op->tmp2_live)) ws.push_back(q);
+  size_t wi = 0;
+  auto take_ws = [&]() { return wi < ws.size() ? ws[wi++] : nullptr; };
   void* ybuf3[3] = {op->ybuf[0], op->ybuf[1], take_ws()};
   double* pbuf[3];
   // launch L covers terms first_term(L) + 1 .. first_term(L + 1)
   const int depth = kPipeMax, lead = depth - (stage_u ? 1 : 0);
   auto first_term = [&](int L) { return L == 0 ? 0 : std::min(maxdeg, lead + (L - 1) * depth); };
   auto launch_of = [&](int term) { return term <= lead ? 0 : 1 + (term - lead - 1) / depth; };
-  const int lpred = launch_of(predicted);                 // the launch with the predicted degree
-  const bool inside = first_term(lpred + 1) != predicted;  // ... and whether it runs past it
-  for (int i = 0; i < 3; ++i) pbuf[i] = !inside && i == lpred % 3 ? p_out : take_ws();
+  const int lpred = launch_of(predicted);  // the launch with the predicted degree
+  auto inside = [&](int m) { return first_term(launch_of(m) + 1) != m; };  // its launch runs past it
+  // degrees inside a launch whose p is stored, and where: the predicted one in
+  // p_out if that leaves three vectors for the launches
+  int mark[2] = {0, 0};
+  double* markp[2] = {p_out, nullptr};
+  if (inside(predicted) && ws.size() - wi >= 3) mark[0] = predicted;
+  for (int i = 0; i < 3; ++i) pbuf[i] = !mark[0] && i == lpred % 3 ? p_out : take_ws();
+  const int before = std::min(P.prev_degree, maxdeg);
+  if (before > 0 && before != predicted && inside(before) && (markp[1] = take_ws())) mark[1] = before;
   std::vector<int> lk, ln;
   PipeArgs a{};
   a.invg = P.invg;
@@ -587,7 +597,8 @@ static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, do
       set_launch(L, kcov, n);
       a.yout = ybuf3[(L + 1) % 3];
       a.pst[a.nst - 1] = pbuf[L % 3];
-      if (inside && L == lpred) a.pst[predicted - kcov - 1 + a.stage] = p_out;
+      for (int i = 0; i < 2; ++i)
+        if (mark[i] > kcov && mark[i] < kcov + n) a.pst[mark[i] - kcov - 1 + a.stage] = markp[i];
       a.slot = L & 1;
       HIPCHK(launch_pipe(op->f, a, st));
       a.nb_prev = a.nblocks;
@@ -646,15 +657,18 @@ static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, do
   out.degree = op->host_ctl->degree;
   out.status = op->host_ctl->stop ? op->host_ctl->status : 3;
   if (out.status != 1) return ADL_OK;
-  const int m = P.last_degree = out.degree;
+  const int m = out.degree;
+  if (m != P.last_degree) P.prev_degree = P.last_degree;
+  P.last_degree = m;
+  out.p = p_out;
   if (m == 0) {
     HIPCHK(launch_fill(op->n, p_out, 0.0, st));
     return ADL_OK;
   }
   const int Ls = launch_of(m);
   double* res = pbuf[Ls % 3];
-  if (inside && m == predicted) {
-    res = p_out;
+  if (m == mark[0] || m == mark[1]) {
+    res = markp[m == mark[0] ? 0 : 1];
   } else if (m != lk[Ls] + ln[Ls]) {
     // the sweep stopped inside launch Ls: replay it up to term m on its inputs
     // (intact: the launch beside the decision of launch Ls wrote neither, and
@@ -669,7 +683,8 @@ static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, do
     a.replay = 1;
     HIPCHK(launch_pipe(op->f, a, st));
   }
-  if (res != p_out) HIPCHK(launch_axpby(op->n, p_out, 1.0, res, 0.0, nullptr, st));
+  if (out.anywhere) out.p = res;
+  else if (res != p_out) HIPCHK(launch_axpby(op->n, p_out, 1.0, res, 0.0, nullptr, st));
   return ADL_OK;
 }
 
@@ -1022,6 +1037,8 @@ static int combo_fixed(adl_op* op, const double* w1, const double* w2, double dt
       f = op->tmp;
     }
     SweepOut so;
+    so.anywhere = true;
+    so.p = op->p;
     // (stage_u: w1 = A stage_u + stage_s is formed by the sweep's first launch; K = 1)
     RETCHK(sweep(op, P, f, w2, 1.0 / dt, op->p, tol, op->max_degree, st, so, j == 0 ? stage_u : nullptr,
                  j == 0 ? stage_s : nullptr));
@@ -1032,12 +1049,12 @@ static int combo_fixed(adl_op* op, const double* w1, const double* w2, double dt
       return ADL_OK;
     }
     if (K == 1 && u_direct) {
-      HIPCHK(launch_axpby(op->n, u_direct, 1.0, u_direct, h, op->p, st));
+      HIPCHK(launch_axpby(op->n, u_direct, 1.0, u_direct, h, so.p, st));
       *applied = true;
     } else if (j == 0) {
-      HIPCHK(launch_axpby(op->n, op->yacc, h, op->p, 0.0, nullptr, st));
+      HIPCHK(launch_axpby(op->n, op->yacc, h, so.p, 0.0, nullptr, st));
     } else {
-      HIPCHK(launch_axpby(op->n, op->yacc, 1.0, op->yacc, h, op->p, st));
+      HIPCHK(launch_axpby(op->n, op->yacc, 1.0, op->yacc, h, so.p, st));
     }
   }
   return ADL_OK;
@@ -1681,7 +1698,9 @@ static int quad2_impl(adl_op* op, double* u, const double* S1, const double* S2,
       acc.substeps = s1.substeps;
       if (w2) {
         // phi_2 result into w1 (w1 is no longer needed)
+        op->tmp2_live = true;
         code = adl_leja_phi(op, 2, dt, w2, op->w1, tol, 0, &s2, stream);
+        op->tmp2_live = false;
         if (code == ADL_OK) {
           acc.matvecs += s2.matvecs;
           acc.sweeps += s2.sweeps;

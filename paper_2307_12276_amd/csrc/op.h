@@ -24,6 +24,7 @@ struct Plan {
   std::vector<double> s;      // augmented scalars s_k
   double invg = 0.0;
   int last_degree = -1;
+  int prev_degree = -1;       // the last one that differed from it
 };
 
 
@@ -54,6 +55,7 @@ struct adl_op {
   Tiling t41{}; // four-term kernel, one column per lane
   int fuse_terms = 1;  // 0 one Newton term per launch, 1 the pipeline (up to seven), 2 two (LDS-staged), 3 two (frames),
                        // 4 four (frames), 5 three (LDS-staged), 6 four (LDS-staged)
+  bool tmp2_live = false;  // tmp2 holds a result across a sweep (two-sweep quadrature)
   int streaming = -1;  // non-temporal hints on Newton vectors: -1 auto, 0 off, 1 on
   int nx = 0, ny = 0, bc = 0, storage = 0;
   double hx = 0, hy = 0;

@@ -84,3 +84,31 @@ def test_pipeline_matches_one_term_launches(nx, ny, storage, field, bc):
         tol = 1e-5 if storage == 2 else max(1e-13, 4e-15 * db)
         assert np.isfinite(a).all()
         assert np.linalg.norm(a - b) <= tol * max(np.linalg.norm(b), peak)
+
+
+@pytest.mark.parametrize("bc", [O.PERIODIC, O.DIRICHLET])
+def test_two_sweeps_with_substeps_keep_the_first_result(bc):
+    """Two-sweep quadrature steps in several substeps: the second evaluation's
+    sweeps must leave the vector that holds the first one's result alone."""
+    nx, ny = 64, 48
+    Dxx, Dxy, Dyy, ax, ay = W.random_fields(nx, ny, seed=3, field_advection=False)
+    oop, gop = make_pair(Dxx, Dxy, Dyy, ax, ay, 1.0 / nx, 0.8 / ny, bc, 0)
+    alpha = bounds.gershgorin(oop)
+    gop.set_bound(alpha)
+    gop.set_limits(500, 20.0)
+    gop.set_quad2_mode(A.QUAD2_TWO_SWEEP)
+    u0, S0 = W.random_vector((ny, nx), 13), W.random_vector((ny, nx), 3)
+    S = to_dev(S0)
+    dt = 70.0 / abs(alpha)
+    got = {}
+    for mode in (0, 1):
+        gop.set_term_fusion(mode)
+        u, mv = to_dev(u0), []
+        for _ in range(3):
+            mv.append(gop.quad2_step(u, S, 3 * S, 1 / 3, 2 / 3, dt, 1e-10)["matvecs"])
+        got[mode] = to_np(u), mv
+    # (three steps of two evaluations whose partial sums are up to 20 / 2 times
+    # their results, rho h = 20: 4e-15 per term of each)
+    a, b = got[1][0], got[0][0]
+    assert got[0][1] == got[1][1]
+    assert np.linalg.norm(a - b) <= 10 * 4e-15 * sum(got[0][1]) * np.linalg.norm(b)
