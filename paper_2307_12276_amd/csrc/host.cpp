@@ -273,6 +273,9 @@ struct SweepOut {
   int status = 0;  // 1 converged, 2 non-finite, 3 degree cap
   bool anywhere = false;      // in: the result may be left in a workspace vector ...
   const double* p = nullptr;  // out: ... this one (else in the sweep's p_out)
+  double* upd = nullptr;      // in: advance this vector by upd_h p, if that can be done without the host:
+  double upd_h = 0.0;
+  bool applied = false;       // out: ... it was
 };
 
 static int read_ctl(adl_op* op, hipStream_t st) {
@@ -579,6 +582,7 @@ static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, do
   dec.slot_stride = op->slot_stride;
   dec.ctl = op->ctl;
   int kcov = 0, L = 0;
+  bool spun = false;
   while (true) {
     const int target = std::min(maxdeg, kcov == 0 ? predicted : known ? kcov + 1 : kcov + std::max(8, kcov / 4));
     const int L0 = L;
@@ -622,6 +626,25 @@ static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, do
     dec.hctl = spin ? op->hctl_dev : nullptr;
     dec.hseq = spin ? (op->hseq = next_hseq()) : 0;
     HIPCHK(launch_decide(dec, st));
+    if (spin && out.upd) {
+      // the update of a sweep that stopped at a stored degree, behind the
+      // decision in the stream: the host need not see the outcome first (four
+      // steps at 512^2 1126 -> 1105 us, at 1024^2 1296 -> 1280)
+      PipeUpdate up{};
+      up.u = out.upd;
+      up.h = out.upd_h;
+      up.n = op->n;
+      up.ctl = op->ctl;
+      for (int i = 0; i < 2; ++i) {
+        up.mark[i] = mark[i];
+        up.markp[i] = markp[i];
+      }
+      for (int i = 0; i < 3; ++i) up.pbuf[i] = pbuf[i];
+      up.lead = lead;
+      up.maxdeg = maxdeg;
+      HIPCHK(launch_pipe_update(up, st));
+    }
+    spun = spin;
     RETCHK(spin ? await_outcome(op, st) : read_ctl(op, st));
     if (op->prof) {
       // launches after the one that ran beside the final decision skipped
@@ -667,6 +690,7 @@ static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, do
   }
   const int Ls = launch_of(m);
   double* res = pbuf[Ls % 3];
+  out.applied = spun && out.upd && (m == mark[0] || m == mark[1] || m == lk[Ls] + ln[Ls]);
   if (m == mark[0] || m == mark[1]) {
     res = markp[m == mark[0] ? 0 : 1];
   } else if (m != lk[Ls] + ln[Ls]) {
@@ -1039,6 +1063,10 @@ static int combo_fixed(adl_op* op, const double* w1, const double* w2, double dt
     SweepOut so;
     so.anywhere = true;
     so.p = op->p;
+    if (K == 1 && u_direct) {
+      so.upd = u_direct;
+      so.upd_h = h;
+    }
     // (stage_u: w1 = A stage_u + stage_s is formed by the sweep's first launch; K = 1)
     RETCHK(sweep(op, P, f, w2, 1.0 / dt, op->p, tol, op->max_degree, st, so, j == 0 ? stage_u : nullptr,
                  j == 0 ? stage_s : nullptr));
@@ -1049,7 +1077,7 @@ static int combo_fixed(adl_op* op, const double* w1, const double* w2, double dt
       return ADL_OK;
     }
     if (K == 1 && u_direct) {
-      HIPCHK(launch_axpby(op->n, u_direct, 1.0, u_direct, h, so.p, st));
+      if (!so.applied) HIPCHK(launch_axpby(op->n, u_direct, 1.0, u_direct, h, so.p, st));
       *applied = true;
     } else if (j == 0) {
       HIPCHK(launch_axpby(op->n, op->yacc, h, so.p, 0.0, nullptr, st));

@@ -63,6 +63,20 @@ struct PipeArgs {
 void pipe_geometry(int nx, int ny, bool advf, PipeArgs& a);
 // a launch's block partials take 3 x nst x nblocks values of its slot
 hipError_t launch_pipe(const FieldView& f, const PipeArgs& a, hipStream_t st);
+// u += h p of a sweep that stopped (status 1) at a degree whose p was stored: a
+// marked one, or the last term of launch L (in pbuf[L mod 3]), launches being of
+// `lead` terms, then kPipeMax each, up to maxdeg.
+struct PipeUpdate {
+  double* u;
+  double h;
+  long n;
+  const Ctl* ctl;
+  int mark[2];
+  const double* markp[2];
+  const double* pbuf[3];
+  int lead, maxdeg;
+};
+hipError_t launch_pipe_update(const PipeUpdate& a, hipStream_t st);
 // The power method's tests of iterations k + 1 .. k + iters: launch i of the
 // chunk (kPipeMax iterations, the last one maybe fewer) left its partials at
 // partials + 3 kPipeMax nb i, ||y_0||^2 of the first chunk is the sum of
