@@ -154,7 +154,8 @@ int adl_op_set_tiling(adl_op* op, int rows, int cols_per_lane);
  * default) computes up to seven terms per launch, the first launch included,
  * as a pipeline of waves along the rows (y_{k+1} .. y_{k+6} and the p between
  * handed on through LDS; read y_k, the fields and p_k once, write y_{k+7} and
- * p_{k+7}); a midpoint step without substeps forms its stage vector A u + S in
+ * p_{k+7}), or on small grids (up to about 320^2) on tiles held in registers
+ * with a frame of seven points; a midpoint step without substeps forms its stage vector A u + S in
  * the first launch.  On grids of 2^28 points and more it computes three (mode
  * 5's form; with FP64 Newton vectors and no augmented column among terms
  * 1 .. 3 the first launch takes three terms too and forms the stage vector),

@@ -22,6 +22,13 @@ constexpr int kPipeBlocks1 = 255, kPipeBlocks2 = 511, kPipeRows1 = 40;
 // grids of fewer points: every byte offset of an FP64 vector below 2^31
 constexpr long kPipePoints = 1L << 28;
 
+// a launch's MODE: a later one, or a first one (p_0 = d0 y_0), maybe with an
+// added row (src) and with the stage vector as its first stage
+enum { PIPE_LATER = 0, PIPE_FIRST = 1, PIPE_SRC = 2, PIPE_STAGE = 4 };
+
+// the points a block of the tile kernel owns (pipe_tile.hip)
+constexpr int kTileCols = kWave - 2 * kPipeMax, kTileRows = 24 - 2 * kPipeMax;
+
 // One launch: stages 1 .. nst on y_0 = yin.  Stage t computes
 //   y_t = ((A y_{t-1} + srcc src) - shift[t-1] y_{t-1}) invg,
 //   p_t = p_{t-1} + dk[t-1] y_t
@@ -43,6 +50,7 @@ struct PipeArgs {
   int f32y;          // Newton vectors stored as float
   int stream;        // non-temporal hints on p_0 and the stored vectors
   int pair;          // rows readable two columns at a time (nx even, 16-byte aligned vectors)
+  int tile;          // the tile kernel's launch
   int rows;          // rows per run
   int ncb, nblocks;  // strips, worker blocks
   // the decision of the previous launch (leja_decide) and this launch's partials
@@ -59,10 +67,12 @@ struct PipeArgs {
   __host__ __device__ double dk_of(int t) const { return dk[t - 1]; }
   __host__ __device__ double* p_of(int t) const { return pst[t - 1]; }
 };
-// rows, ncb and nblocks of a launch on an nx x ny grid
+// tile, rows, ncb and nblocks of a launch on an nx x ny grid
 void pipe_geometry(int nx, int ny, bool advf, PipeArgs& a);
 // a launch's block partials take 3 x nst x nblocks values of its slot
 hipError_t launch_pipe(const FieldView& f, const PipeArgs& a, hipStream_t st);
+// (launch_pipe's, for a.tile)
+hipError_t launch_tile(const FieldView& f, const PipeArgs& a, hipStream_t st);
 // u += h p of a sweep that stopped (status 1) at a degree whose p was stored: a
 // marked one, or the last term of launch L (in pbuf[L mod 3]), launches being of
 // `lead` terms, then kPipeMax each, up to maxdeg.

@@ -7,7 +7,11 @@
 
 namespace adl {
 
-// One block per CU where that leaves a block at most kPipeRows1 rows, else two:
+// The tile kernel where its blocks are at most one per CU: a sweep of 89 terms,
+// us, on the pipeline / tiles: 256^2 159 / 148, 320^2 162 / 149 (224 tiles), 384^2
+// 180 / 190 (312 tiles), 512^2 202 / 258, 1024^2 350 / 610; 64^2 146 / 146.
+constexpr long kTileBlocks = 255;
+// Else the pipeline.  One block per CU where that leaves a block at most kPipeRows1 rows, else two:
 // two share a CU's issue slots but halve the rows, and a launch takes rows + 21
 // ticks.  A sweep of 89 terms, us, with 255 / 511 blocks: 256^2 173 / 199, 512^2
 // 213 / 233, 896^2 (29 rows) 313 / 321, 2048 x 512 (40 rows) 365 / 362, 1024^2
@@ -15,6 +19,14 @@ namespace adl {
 // advection fields two blocks' LDS (98 KB each) does not fit a CU: 1001 x 777
 // step 486 / 664.
 void pipe_geometry(int nx, int ny, bool advf, PipeArgs& a) {
+  const long tiles = (long)((nx + kTileCols - 1) / kTileCols) * ((ny + kTileRows - 1) / kTileRows);
+  a.tile = tiles <= kTileBlocks;
+  if (a.tile) {
+    a.ncb = (nx + kTileCols - 1) / kTileCols;
+    a.rows = kTileRows;
+    a.nblocks = (int)tiles;
+    return;
+  }
   a.ncb = (nx + kPipeCols - 1) / kPipeCols;
   auto rows = [&](int blocks) {
     int runs = blocks / a.ncb;
@@ -30,7 +42,8 @@ void pipe_geometry(int nx, int ny, bool advf, PipeArgs& a) {
 hipError_t launch_pipe(const FieldView& f, const PipeArgs& a, hipStream_t st) {
   // (float Newton vectors come with float fields)
   if ((long)f.nx * f.ny >= kPipePoints || (a.f32y && !f.f32)) return hipErrorInvalidValue;
-  if (a.nst < 1 || a.nst > kPipeMax || a.rows < 1 || a.ncb * kPipeCols < f.nx ||
+  if (a.nst < 1 || a.nst > kPipeMax || a.rows < 1 || a.ncb * (a.tile ? kTileCols : kPipeCols) < f.nx ||
+      (a.tile && a.rows != kTileRows) ||
       a.nblocks != a.ncb * ((f.ny + a.rows - 1) / a.rows))
     return hipErrorInvalidValue;
   // (a replay writes no partials)
@@ -50,6 +63,7 @@ hipError_t launch_pipe(const FieldView& f, const PipeArgs& a, hipStream_t st) {
       if (a.pst[i] == a.pst[t]) return hipErrorInvalidValue;
   }
   if (!any) return hipErrorInvalidValue;
+  if (a.tile) return launch_tile(f, a, st);
   return f.f32 ? launch_pipe_fields<float>(f, a, st) : launch_pipe_fields<double>(f, a, st);
 }
 

@@ -51,9 +51,6 @@ namespace adl {
 
 constexpr int kPipeRow = kWave * 2;  // doubles of an LDS row
 
-// a launch's MODE: a later one, or a first one (p_0 = d0 y_0), maybe with an
-// added row (src) and with the stage vector as its first stage
-enum { PIPE_LATER = 0, PIPE_FIRST = 1, PIPE_SRC = 2, PIPE_STAGE = 4 };
 
 __device__ __forceinline__ void pipe_put(double* row, const double (&c)[2]) {
   typedef double d2 __attribute__((ext_vector_type(2)));
@@ -253,9 +250,25 @@ __device__ __forceinline__ void pipe_inside(const FieldView& F, const PipeRun& r
   left = c < 0;
 }
 
-// Wave 0: the rows a0 .. J1 - 1 + nst into LDS.
+// The stop flag as one wave read it, the same for the whole block, which its
+// barriers need (an LDS word that the first puts overwrite).
+__device__ __forceinline__ bool pipe_stopped(double* lds, int flag, bool mine) {
+  int* const word = reinterpret_cast<int*>(lds);
+  if (mine) *word = flag;
+  __syncthreads();
+  const int stop = __builtin_amdgcn_readfirstlane(*word);
+  __syncthreads();
+  return stop != 0;
+}
+
+// Wave 0: the rows a0 .. J1 - 1 + nst into LDS.  stop: the sweep's stop flag, or
+// null; it is read ahead of the first rows, whose loads are in flight while the
+// block waits for it (read before them it cost 1 us a launch).
 template <typename TF, typename TYI, bool ADVF, bool PAIR, bool NT, int MODE, class Args>
-__device__ __forceinline__ void pipe_loader(const FieldView& F, const Args& A, double* lds, const PipeRun& r) {
+__device__ __forceinline__ void pipe_loader(const FieldView& F, const Args& A, double* lds, const PipeRun& r,
+                                            const int* stop) {
+  int flag = 0;
+  if (stop) flag = __hip_atomic_load(stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int lane = threadIdx.x & (kWave - 1);
   const bool per = F.bc == BC_PERIODIC;
   constexpr int NC = kPipeCoef<ADVF>;
@@ -316,6 +329,7 @@ __device__ __forceinline__ void pipe_loader(const FieldView& F, const Args& A, d
   };
 #pragma unroll
   for (int i = 0; i < kPipeAhead; ++i) load(set[i]);
+  if (stop && pipe_stopped(lds, flag, lane == 0)) return;
   double gp[2] = {0.0, 0.0}, yp[2] = {0.0, 0.0};  // kyy and y of the row before
   int row = r.a0, slot = 0;  // the row to put, where its coefficients go
   auto put = [&](Set& s, int par) {
@@ -405,7 +419,8 @@ __device__ __forceinline__ void pipe_loader(const FieldView& F, const Args& A, d
 // stage 1, which takes the added row, forms the stage vector and whether y_0 is zero).
 template <typename TY, bool ADVF, bool PAIR, bool NT, int MODE, class Args>
 __device__ __forceinline__ void pipe_stage(const FieldView& F, const Args& A, double* lds, const PipeRun& r, int t,
-                                           int b) {
+                                           int b, const int* stop) {
+  if (stop && pipe_stopped(lds, 0, false)) return;
   const int lane = threadIdx.x & (kWave - 1);
   constexpr int NC = kPipeCoef<ADVF>;
   const int nst = r.nst, ring = 2 * nst * NC * kPipeRow;
@@ -592,25 +607,13 @@ __global__ __launch_bounds__(kPipeThreads, ADVF ? 2 : 4) void pipe_kernel(FieldV
     }
     return;
   }
-  if constexpr (MODE == PIPE_LATER) {
-    // one read of the stop flag for the whole block, which its barriers need
-    // (an LDS word that the first puts overwrite two barriers later)
-    if (!A.replay) {
-      int* flag = reinterpret_cast<int*>(lds);
-      if (threadIdx.x == 0)
-        *flag = __hip_atomic_load(&A.ctl->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __syncthreads();
-      const int stop = __builtin_amdgcn_readfirstlane(*flag);
-      if (stop) return;
-      __syncthreads();
-    }
-  }
+  const int* const stop = MODE == PIPE_LATER && !A.replay ? &A.ctl->stop : nullptr;
   const PipeRun r = pipe_run(F, A, L - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   using TYI = std::conditional_t<MODE == PIPE_LATER, TY, double>;
-  if (wave == 0) pipe_loader<TF, TYI, ADVF, PAIR, NT, MODE>(F, A, lds, r);
-  else if (MODE != PIPE_LATER && wave == 1) pipe_stage<TY, ADVF, PAIR, NT, MODE>(F, A, lds, r, 1, L - 1);
-  else pipe_stage<TY, ADVF, PAIR, NT, PIPE_LATER>(F, A, lds, r, wave, L - 1);
+  if (wave == 0) pipe_loader<TF, TYI, ADVF, PAIR, NT, MODE>(F, A, lds, r, stop);
+  else if (MODE != PIPE_LATER && wave == 1) pipe_stage<TY, ADVF, PAIR, NT, MODE>(F, A, lds, r, 1, L - 1, stop);
+  else pipe_stage<TY, ADVF, PAIR, NT, PIPE_LATER>(F, A, lds, r, wave, L - 1, stop);
 }
 
 template <typename TF, typename TY, bool ADVF, bool PAIR, bool NT, int MODE>

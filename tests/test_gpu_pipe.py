@@ -1,7 +1,7 @@
 """The pipeline kernel (the default mode: seven Newton terms per launch, the
 stage vector in the first launch) against one-term launches of the same sweep,
 at the edges of its strips (112 own columns, two columns per lane) and runs of
-rows, and against one-term launches' degrees.
+rows, and of the tiles that small grids take (50 x 10 own points), and against one-term launches' degrees.
 
 Tolerance: both orders of summation stay within a few 1e-15 of the exact
 Newton sum per term taken, so 4e-15 per term (at least 1e-13); Newton vectors
@@ -22,7 +22,11 @@ from oracle import operator as O
 pytestmark = pytest.mark.gpu
 
 SHAPES = [
-    (16, 12),      # a fraction of one strip, fewer rows than blocks
+    (16, 12),      # a fraction of one tile (50 x 10 points)
+    (50, 10),      # one whole tile
+    (51, 11),      # ... and one column and one row more
+    (250, 510),    # 255 tiles, the most
+    (250, 511),    # one row more: the pipeline
     (33, 45),      # odd width: columns loaded one by one
     (112, 3),      # one whole strip, three rows
     (113, 40),     # ... and one column more
