@@ -84,8 +84,8 @@ def device_sources(w):
     return srcs
 
 
-KERNEL_SOURCES = ("device.h", "internal.h", "stencil.hip", "tile.h", "staged.h")
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "leja3s_kernel_stream4096_traffic.txt")
+KERNEL_SOURCES = ("device.h", "internal.h", "tile.h", "decide.h", "pipe.h", "pipe_kernel.h", "pipe.hip")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pipe_kernel_stream4096_traffic.txt")
 TRAFFIC_KEY = "traffic_bytes_per_launch_stream4096"
 BYTES_PER_TERM_FP64 = 56.0  # read y, Dxx, Dxy, Dyy, p; write y, p (FP64, constant advection)
 
@@ -114,7 +114,7 @@ def traffic_record():
 
 
 def measured_traffic():
-    """HBM bytes per three-term Newton-Leja launch of the 4096^2 workload from
+    """HBM bytes per Newton-Leja launch of the 4096^2 workload (seven terms) from
     the committed rocprofv3 FETCH_SIZE / WRITE_SIZE summary, or None when the
     kernel sources have changed since those counters were taken."""
     kv = traffic_record()
@@ -133,14 +133,11 @@ def kernel_roofline(op_ms, launches, nbytes):
     return avg_ms, per_launch, achieved
 
 
-KIND_KERNELS = {"two": "leja2s_kernel (two Newton terms per launch, input rows staged in LDS, non-temporal "
-                        "hints on the vectors read or written once)",
-                "three": "leja3s_kernel (three Newton terms per launch, input rows staged in LDS, non-temporal "
-                         "hints on the vectors read or written once)",
-                "four": "leja4_kernel (four Newton terms per launch)"}
+PIPE_KERNEL = ("pipe_kernel (up to seven Newton terms per launch as a pipeline of waves, the first launch with the "
+               "stage vector, non-temporal hints on the vectors read or written once)")
 
 LEG_KERNELS = {0: ("one-term", "leja_kernel"),
-               1: ("three-term (the default)", "leja3s_kernel (input rows staged in LDS) + leja_kernel (first term)"),
+               1: ("up to seven terms (the default)", "pipe_kernel"),
                2: ("two-term", "leja2s_kernel (input rows staged in LDS) + leja_kernel (first term)"),
                3: ("two-term, register frames", "leja2_kernel + leja_kernel (first term)"),
 }
@@ -150,8 +147,8 @@ def run_roofline_leg(w, storage, mode=1):
     """Midpoint steps of the stream-function field at n x n (two warm-up
     steps, three timed): the Newton-Leja kernels' dispatch-timed bandwidth on
     a working set far beyond the caches, with one term per launch (mode 0),
-    the library's choice at this size (mode 1: three terms per launch, input
-    rows staged in LDS), two with staged rows (mode 2) or two with register
+    the library's choice (mode 1: the pipeline, up to seven terms per
+    launch), two with staged rows (mode 2) or two with register
     frames (mode 3)."""
     import torch
     import paper_2307_12276_amd as A
@@ -391,7 +388,7 @@ def profile_leja(n, mode=1, fp32=False):
 
 def profile_c2(steps=5):
     """A few steps of the 512^2 Dirichlet two-stage quadrature workload
-    alone (four Newton terms per launch), for rocprofv3."""
+    alone, for rocprofv3."""
     import torch
     import paper_2307_12276_amd as A
     import workloads as W
@@ -530,7 +527,7 @@ def cpu_baseline_sample(w, budget_s, matvecs_per_step):
 
 def c2_leg(steps=50, warmup=2, cpu_budget=0.0):
     """The 512^2 Dirichlet two-stage quadrature workload (working set in
-    L2/MALL, four Newton terms per launch): steps/s, the Newton-Leja launches
+    L2/MALL): steps/s, the Newton-Leja launches
     from HIP events on a second pass, and the GPU's error against the
     oracle on the first steps (with the oracle's steps/s) when cpu_budget > 0."""
     import numpy as np
@@ -555,7 +552,6 @@ def c2_leg(steps=50, warmup=2, cpu_budget=0.0):
     for n in range(warmup + steps, warmup + 2 * steps):
         gpu_step(op, w, u, n, srcs)
     torch.cuda.synchronize()
-    ms4, n4, b4, t4 = op.profile_read_kind(A.LAUNCH_FOUR)
     ms, launches, nbytes = op.profile_read()
     op.profile(False)
     res = {"workload": "dirichlet-circular-512: Dirichlet 512x512, circular b, k_par/k_perp=1e3, a=(0.2,0), "
@@ -563,12 +559,9 @@ def c2_leg(steps=50, warmup=2, cpu_budget=0.0):
                        "dt=200 dt_CFL, tol=1e-10, FP64",
            "steps": steps, "steps_per_s": steps / el, "matvecs_per_step": mv / steps,
            "leja_launches": launches, "avg_leja_launch_us": 1e3 * ms / max(launches, 1),
-           "four_term_launches": n4, "avg_four_term_launch_us": 1e3 * ms4 / max(n4, 1),
-           "four_term_GBs_8d": (BYTES_PER_TERM_FP64 * w.nx * w.ny * t4 / max(n4, 1))
-           / (ms4 / max(n4, 1) * 1e-3) / 1e9 if n4 else None,
-           "note": "~15 MB per Newton term: L2/MALL-resident, launch-latency bound"}
-    log("512^2 leg: %.1f steps/s, %.1f matvecs/step, four-term launches %.2f us avg"
-        % (res["steps_per_s"], res["matvecs_per_step"], res["avg_four_term_launch_us"]))
+           "note": "~15 MB per launch of seven terms: L2/MALL-resident, latency bound"}
+    log("512^2 leg: %.1f steps/s, %.1f matvecs/step, launches %.2f us avg"
+        % (res["steps_per_s"], res["matvecs_per_step"], res["avg_leja_launch_us"]))
     if cpu_budget > 0:
         cw = W.c2_dirichlet_circular(n=512, steps=steps)
         rate, nst, el_cpu, u_cpu = cpu_baseline_c2(cw, cpu_budget)
@@ -669,20 +662,19 @@ def headline(args):
     el_prof = time.perf_counter() - t1
     kinds = {k: op.profile_read_kind(getattr(A, "LAUNCH_" + k.upper()))
              for k in ("first", "one", "two", "three", "four")}
-    op.profile_read()
+    # every Newton-Leja launch: its time, and the bytes a launch cannot do
+    # without (one pass over memory for all of its terms)
+    ms2, n2, fused2 = op.profile_read()
     op.profile(False)
-    # the dominant launch kind (the most kernel time): three terms per launch
-    dom = max(("two", "three", "four"), key=lambda k: kinds[k][0])
-    ms2, n2, fused2, terms2 = kinds[dom]
-    N = w.nx * w.ny
+    terms2 = sum(k[3] for k in kinds.values())
     avg_s = ms2 / max(n2, 1) * 1e-3
-    alg = BYTES_PER_TERM_FP64 * N * terms2 / max(n2, 1)
+    alg = fused2 / max(n2, 1)
     achieved = alg / avg_s / 1e9 if n2 else 0.0
     traffic = measured_traffic()
     value = args.steps / el
-    log("headline: %d steps in %.3fs: %.2f steps/s, %.1f matvecs/step; %s-term launches %.1f us avg over %d "
-        "(%.2f terms each): %.0f GB/s by 56 B/pt/term (%.1f%% of 8 TB/s)"
-        % (args.steps, el, value, mv / args.steps, dom, avg_s * 1e6, n2, terms2 / max(n2, 1), achieved,
+    log("headline: %d steps in %.3fs: %.2f steps/s, %.1f matvecs/step; launches %.1f us avg over %d "
+        "(%.2f terms each): %.0f GB/s by 56 B/pt/launch (%.1f%% of 8 TB/s)"
+        % (args.steps, el, value, mv / args.steps, avg_s * 1e6, n2, terms2 / max(n2, 1), achieved,
            100 * achieved / HBM_PEAK_GBS))
     out = {
         "metric": METRIC, "value": value, "unit": "steps/s", "n_gpus": 1,
@@ -696,13 +688,15 @@ def headline(args):
                    "matvecs_per_step": mv / args.steps, "matvecs_per_s": mv / el, "setup_s": setup_s},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": KIND_KERNELS[dom],
-                     "bytes_per_launch": alg, "bytes_rule": "56 B per point and Newton term (FP64) x %d points "
-                                                           "x %.2f terms per launch" % (N, terms2 / max(n2, 1)),
+                     "kernel": PIPE_KERNEL,
+                     "bytes_per_launch": alg, "bytes_rule": "56 B per point and launch (FP64: read y, the fields and "
+                                                           "p, write y and p once for %.2f terms per launch)"
+                                                           % (terms2 / max(n2, 1)),
                      "avg_kernel_us": avg_s * 1e6, "launches": n2,
-                     "fused_bytes_per_launch": fused2 / max(n2, 1),
-                     "timing": "HIP events on each %s-term dispatch, second pass of %d steps (%.3fs)"
-                               % (dom, args.steps, el_prof),
+                     "terms_per_launch": terms2 / max(n2, 1),
+                     "timing": "HIP events on each Newton-Leja dispatch, second pass of %d steps (%.3fs); in "
+                               "launch_kinds a launch of more than three terms counts as groups of three and a "
+                               "remainder" % (args.steps, el_prof),
                      "traffic_source": "profiles/%s (rocprofv3 FETCH_SIZE and WRITE_SIZE per dispatch, "
                                        "scaled by a 1 GiB copy), bytes per launch" % os.path.basename(TRAFFIC_FILE)},
         "launch_kinds": {k: {"launches": v[1], "avg_us": 1e3 * v[0] / v[1] if v[1] else None, "terms": v[3]}
