@@ -2029,29 +2029,28 @@ int upload_bins(adl_batch* B, double* const* u, const double* const* S, double d
     if (B->total_blocks3 > 0)
       BCHK(hipMemcpy(B->d_block_bin3, B->block_bin3.data(), sizeof(int) * B->total_blocks3, hipMemcpyHostToDevice));
   }
-  if (pipe) {
-    if (changed || plans_changed) {
-      bool even = true;
-      int src = 0;
-      double bytes = 0.0;
-      for (int b = 0; b < B->nbins; ++b) {
-        const BinDesc& d = B->bins[b];
-        even &= d.f.nx % 2 == 0 && !(reinterpret_cast<uintptr_t>(d.u) & 15) && !(reinterpret_cast<uintptr_t>(d.S) & 15);
-        src |= d.S != nullptr;
-        // (fields, u, S, three y and p each)
-        bytes += ((B->advf ? 5.0 : 3.0) * (B->f32 ? 4.0 : 8.0) + 64.0) * d.f.nx * d.f.ny;
-      }
-      B->pair = even;
-      B->src = src;
-      B->stream = bytes > kStreamMinBytes;
-      B->pdirty = true;
+  if (changed || plans_changed) {
+    bool even = true;
+    int src = 0;
+    double bytes = 0.0;
+    for (int b = 0; b < B->nbins; ++b) {
+      const BinDesc& d = B->bins[b];
+      even &= d.f.nx % 2 == 0 && !(reinterpret_cast<uintptr_t>(d.u) & 15) && !(reinterpret_cast<uintptr_t>(d.S) & 15);
+      src |= d.S != nullptr;
+      // (fields, u, S, three y and p each)
+      bytes += ((B->advf ? 5.0 : 3.0) * (B->f32 ? 4.0 : 8.0) + 64.0) * d.f.nx * d.f.ny;
     }
-    if (pipe_plan(B, dt)) {
-      if (!changed && !plans_changed) BCHK(hipStreamSynchronize(st));
-      plans_changed = true;
-      if (!B->pmap.empty())
-        BCHK(hipMemcpy(B->d_pmap, B->pmap.data(), sizeof(int2) * B->pmap.size(), hipMemcpyHostToDevice));
-    }
+    B->pair = even;
+    B->src = src;
+    B->stream = bytes > kStreamMinBytes;
+    B->pdirty = true;
+  }
+  if (pipe && pipe_plan(B, dt)) {
+    // (a replay of the step before may still read the maps)
+    BCHK(hipStreamSynchronize(st));
+    plans_changed = true;
+    if (!B->pmap.empty())
+      BCHK(hipMemcpy(B->d_pmap, B->pmap.data(), sizeof(int2) * B->pmap.size(), hipMemcpyHostToDevice));
   }
   if (changed || plans_changed) {
     BCHK(hipStreamSynchronize(st));
@@ -2214,7 +2213,7 @@ int autotune_key(const adl_batch* B, const int* candidates, int ncand, std::stri
   std::sort(shapes.begin(), shapes.end());
   key = std::string(prop.gcnArchName) + "|f32=" + std::to_string(B->f32) + "|adv=" + std::to_string((int)B->advf) +
         "|vec=" + std::to_string(B->vec) + "|two=" + std::to_string(B->two) +
-        "|three=" + std::to_string(B->three) + "|pipe=" + std::to_string(B->pipe) + "|cand=";
+        "|three=" + std::to_string(B->three) + "|cand=";
   for (int c = 0; c < ncand; ++c) key += std::to_string(candidates[c]) + ",";
   key += "|bins=";
   for (const auto& sh : shapes) key += std::to_string(sh.first) + "x" + std::to_string(sh.second) + ",";
@@ -2386,7 +2385,8 @@ int adl_batch_get_tile_rows(const adl_batch* B, int* rows) {
   return ADL_OK;
 }
 
-// Project autotuner: time the stage + sweep launches of one step (u is not
+// Project autotuner: time the stage + sweep launches of one step in tiles (a
+// graph step's; a pipeline step uses the tile height in its update alone; u is not
 // modified) for each candidate tile height and keep the fastest.  Results are
 // cached per process by the tuning key (autotune_key): a later call with the
 // same key installs the cached tile height without timing.
@@ -2421,24 +2421,18 @@ int adl_batch_autotune(adl_batch* B, double* const* u, const double* const* S_ha
     int rc = adl_batch_set_tile_rows(B, candidates[c]);
     if (rc != ADL_OK) return rc;
     bool changed;
-    rc = upload_bins(B, u, S_half, dt, tol, B->pipe, st, changed);
+    rc = upload_bins(B, u, S_half, dt, tol, false, st, changed);
     if (rc != ADL_OK) return rc;
     const int nterms = predicted_terms(B, dt);
     float ms_min = INFINITY;
     for (int rep = 0; rep < 3; ++rep) {
-      if (B->pipe) BCHK(hipStreamSynchronize(st));
-      const auto t0 = std::chrono::steady_clock::now();
       BCHK(hipEventRecord(e0, st));
-      rc = B->pipe ? enqueue_pipe(B, 0, st) : enqueue_sweep(B, 0, nterms, true, st, nullptr, false);
+      rc = enqueue_sweep(B, 0, nterms, true, st, nullptr, false);
       if (rc != ADL_OK) return rc;
       BCHK(hipEventRecord(e1, st));
       BCHK(hipEventSynchronize(e1));
       float ms;
       BCHK(hipEventElapsedTime(&ms, e0, e1));
-      // a pipeline sweep, whose launches the tile height does not change, is
-      // timed as a caller waits for it (the events' 10 ns steps cannot tell
-      // two such times apart)
-      if (B->pipe) ms = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - t0).count();
       if (rep > 0) ms_min = std::min(ms_min, ms);
     }
     if (ms_min < bms) {
