@@ -287,14 +287,19 @@ int adl_batch_destroy(adl_batch* b);
 int adl_batch_set_tile_rows(adl_batch* b, int rows);
 int adl_batch_get_tile_rows(const adl_batch* b, int* rows);
 
-/* Newton terms per launch of the batched sweep (Sec. 2 recurrence): mode = 3
- * (the default when every bin has nx even and >= 128) computes terms k+1 ..
+/* Newton terms per launch of the batched sweep (Sec. 2 recurrence).  Until a
+ * mode is set, eager steps (use_graph = 0) run up to seven terms of every
+ * running bin per launch on the pipeline kernel, the stage vector in the first
+ * launch, p stored at the degrees around the bin's last one and a bin that stops
+ * elsewhere replayed up to its stop.  Graph steps, and all steps once a mode is
+ * set, run on tiles: mode = 3 (a graph step's default when every bin has nx even
+ * and >= 128) computes terms k+1 ..
  * k+3 of every running bin in one launch, the first three included, blocks
  * of four waves marching runs of 4 * tile_rows rows of a strip of one bin
  * with the input rows staged in LDS (a launch stores y of its last two terms,
  * the second-to-last in FP32, and p of the last; a bin that stops at an
- * earlier term is advanced by p_m rebuilt from them); mode = 1 (the default
- * otherwise) computes terms k+1 and k+2 in one launch after a launch of the
+ * earlier term is advanced by p_m rebuilt from them); mode = 1 (a graph step's
+ * default otherwise) computes terms k+1 and k+2 in one launch after a launch of the
  * first term alone (one wave per tile marches down its rows with y_{k+1} in
  * registers); mode = 0 launches one kernel per term.  ADL_EINVAL for other
  * values, and for mode 3 when a bin is narrower or odd. */

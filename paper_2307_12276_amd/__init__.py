@@ -460,8 +460,10 @@ class Batch:
 
     def set_term_fusion(self, mode=True):
         """Newton terms per batched launch: 3 three with LDS-staged blocks
-        (the default when every bin has nx even and >= 128), True/1 two after
-        a launch of the first term alone (the default otherwise), False/0 one."""
+        (a graph step's default when every bin has nx even and >= 128), True/1
+        two after a launch of the first term alone (its default otherwise),
+        False/0 one.  Until a mode is set, eager steps run up to seven terms
+        per launch on the pipeline kernel."""
         m = int(mode) if not isinstance(mode, bool) else int(mode)
         _check(lib().adl_batch_set_term_fusion(self.handle, m))
 

@@ -2,6 +2,9 @@
 // sizes, different spectral intervals) advanced by one exponential midpoint
 // step (Sec. 2, eq. 4) together.
 //
+// Eager steps run on the pipeline kernel's blocks by default ("Pipeline sweeps"
+// below).  Graph steps and the modes set by adl_batch_set_term_fusion run on tiles:
+//
 // Work unit: a tile = one wave64 strip of 64*VEC columns x `rows` rows of one
 // bin, which the wave marches down row by row (the windows of rows it needs
 // in registers, the next row's loads in flight).  Every kernel of a step
@@ -10,7 +13,7 @@
 //   term k     y_{k+1} = ((A_b - c_b)/gamma_b - xi_k) y_k,
 //              p_{b,k+1} = p_{b,k} + d_{b,k+1} y_{k+1},
 //              for every bin still running, with the bin's own plan; after
-//              the first term two terms per launch by default (y_{k+1} kept
+//              the first term two terms per launch (y_{k+1} kept
 //              in registers), or three with the input rows staged in LDS
 //              (blocks of four waves march runs of one strip of a bin)
 //   finalize   the decision of the last term, one wave per bin
