@@ -872,7 +872,6 @@ static int sweep(adl_op* op, Plan& P, const double* v, const double* w2, double 
       a.k_prev = prev_k;
       a.nterms_prev = prev_n;
       a.slot_prev = prev_slot;
-      a.decide_only = 0;
       const bool stage = kcov == 0 && stage_u != nullptr;
       if (stage) {
         // the four-stage march: w = A u + s, then terms 1 .. 3 (its p starts
@@ -918,14 +917,13 @@ static int sweep(adl_op* op, Plan& P, const double* v, const double* w2, double 
     a.k_prev = prev_k;
     a.nterms_prev = prev_n;
     a.slot_prev = prev_slot;
-    a.decide_only = 1;
     // outcome: published to the host mirror and awaited by spinning, or (when
     // timing launches with events, which need the stream synchronised, or
     // without a mirror) copied back
     const bool spin = op->hctl && op->host_wait && !op->prof;
     a.hctl = spin ? op->hctl_dev : nullptr;
     a.hseq = spin ? (op->hseq = next_hseq()) : 0;
-    HIPCHK(launch_leja_step(op->f, T, a, st));
+    HIPCHK(launch_decide(a, st));
     a.hctl = nullptr;
     RETCHK(spin ? await_outcome(op, st) : read_ctl(op, st));
     if (op->prof) {
@@ -1003,7 +1001,6 @@ static int sweep(adl_op* op, Plan& P, const double* v, const double* w2, double 
         a.dk3 = n >= 3 ? P.d[k + 3] : 0.0;
         a.dk4 = n == 4 ? P.d[k + 4] : 0.0;
         a.lds_fields = n == 4;
-        a.decide_only = 0;
         a.replay = 1;
         a.hctl = nullptr;
         if (n == 4 && fours) HIPCHK(launch_leja4s_step(op->f, T4s, a, st));

@@ -171,7 +171,6 @@ struct LejaArgs {
   int k_prev;
   int nterms_prev;
   int slot_prev;
-  int decide_only;   // only take the decision of the previous launch (1-block launch)
   Ctl* ctl;
   HostCtl* hctl;     // decision launch: publish the outcome here (device address), or null
   int hseq;          // ... with this sequence number

@@ -15,8 +15,8 @@
 // of that size 180 us) where the three-term staged kernel took 183 us for
 // three; the rest is LDS traffic, 7 KB a row and stage (coefficients, y, p), and
 // issue, two blocks of eight waves a CU.  Up to 1024^2 the latency of rows + 21
-// ticks of about 0.35 us bounds it (256^2: 13 us a launch of seven terms; four
-// terms in LDS took 12.5).  Two rows a tick or two stages a wave gain 7 % at
+// ticks of 0.35 - 0.45 us bounds it (512^2: 16 us a launch of seven terms, where
+// four terms in LDS took 15.4).  Two rows a tick or two stages a wave gain 7 % at
 // 4096^2 but lose 20 - 80 % up to 1024^2 (longer ticks); 3 rows in flight a wave
 // suffice (4 take the same time).
 //

@@ -213,11 +213,10 @@ template <typename TF, typename TYI, typename TYO, int VEC, bool ADVF, bool FIRS
 __global__ __launch_bounds__(kTileBlock) void leja_kernel(FieldView F, Tiling T, LejaArgs A) {
   // XCD-contiguous logical blocks: neighbouring tiles, which share halo
   // columns and rows, run on one XCD and meet in its L2
-  const int L = A.decide_only ? 0 : xcd_contiguous(blockIdx.x, gridDim.x);
+  const int L = xcd_contiguous(blockIdx.x, gridDim.x);
   if (L == 0) {
     if (!FIRST) {
       leja_decide(A);
-      if (A.decide_only && A.hctl && threadIdx.x == 0) publish_outcome(A);
     } else if (threadIdx.x == 0) {
       // a new sweep: clear the control block (no block of this launch reads it)
       Ctl c{};
@@ -359,7 +358,7 @@ __device__ __forceinline__ bool stage1_own(const FieldView& F, const TY* __restr
 template <typename TF, typename TY, int VEC, bool ADVF, bool NT>
 __global__ __launch_bounds__(kTileBlock2) void leja2_kernel(FieldView F, Tiling T, LejaArgs A) {
   extern __shared__ double lds[];
-  const int L = A.decide_only ? 0 : xcd_contiguous(blockIdx.x, gridDim.x);  // as in leja_kernel
+  const int L = xcd_contiguous(blockIdx.x, gridDim.x);  // as in leja_kernel
   if (L == 0) {
     if (!A.replay) leja_decide(A);
     return;
@@ -635,7 +634,7 @@ __global__ __launch_bounds__(kWave * kW4) void leja4_kernel(FieldView F, Tiling 
   // XCD-contiguous logical blocks (row-major: column block fastest): the
   // blocks above and below a block, which load half of its rows again, run
   // on the same XCD and find those rows in its L2
-  const int L = A.decide_only ? 0 : xcd_contiguous(blockIdx.x, gridDim.x);
+  const int L = xcd_contiguous(blockIdx.x, gridDim.x);
   if (L == 0) {
     if (!A.replay) leja_decide(A);
     return;
@@ -755,7 +754,7 @@ __global__ __launch_bounds__(kWave * kW4) void leja4_kernel(FieldView F, Tiling 
 template <typename TF, typename TY, int VEC, bool ADVF, bool NT>
 __global__ __launch_bounds__(kTileBlock2) void leja2s_kernel(FieldView F, Tiling T, LejaArgs A) {
   extern __shared__ double lds[];
-  const int L = A.decide_only ? 0 : xcd_contiguous(blockIdx.x, gridDim.x);
+  const int L = xcd_contiguous(blockIdx.x, gridDim.x);
   if (L == 0) {
     if (!A.replay) leja_decide(A);
     return;
@@ -804,7 +803,7 @@ template <typename TF, typename TY, bool ADVF, bool NT, bool FIRST>
 __global__ __launch_bounds__(kTileBlock2) void leja3s_kernel(FieldView F, Tiling T, LejaArgs A) {
   extern __shared__ __attribute__((aligned(16))) double lds[];  // rows accessed 16 bytes per lane
   constexpr int VEC = 2;
-  const int L = A.decide_only ? 0 : xcd_contiguous(blockIdx.x, gridDim.x);
+  const int L = xcd_contiguous(blockIdx.x, gridDim.x);
   if (L == 0) {
     if (FIRST) {
       // a new sweep: clear the control block (no block of this launch reads it)
@@ -868,7 +867,7 @@ template <typename TF, typename TY, bool ADVF, bool NT, bool STAGE>
 __global__ __launch_bounds__(kTileBlock2) void leja4s_kernel(FieldView F, Tiling T, LejaArgs A) {
   extern __shared__ __attribute__((aligned(16))) double lds[];  // rows accessed 16 bytes per lane
   constexpr int VEC = 2;
-  const int L = A.decide_only ? 0 : xcd_contiguous(blockIdx.x, gridDim.x);
+  const int L = xcd_contiguous(blockIdx.x, gridDim.x);
   if (L == 0) {
     if (STAGE) {
       // a new sweep: clear the control block (no block of this launch reads it)
@@ -1164,7 +1163,7 @@ hipError_t launch_apply(const FieldView& f, const Tiling& t, const double* x, do
 
 template <typename TF, typename TYI, typename TYO, int VEC, bool ADVF, bool FIRST, bool NT>
 static void leja_launch(const FieldView& f, const Tiling& t, const LejaArgs& a, hipStream_t st) {
-  const dim3 grid(a.decide_only ? 1 : t.nblocks + 1), blk(kTileBlock);
+  const dim3 grid(t.nblocks + 1), blk(kTileBlock);
   if (a.ev_start)
     hipExtLaunchKernelGGL((leja_kernel<TF, TYI, TYO, VEC, ADVF, FIRST, NT>), grid, blk, 0, st, a.ev_start,
                           a.ev_stop, 0, f, t, a);
@@ -1174,7 +1173,7 @@ static void leja_launch(const FieldView& f, const Tiling& t, const LejaArgs& a, 
 
 template <typename TF, int VEC, bool ADVF>
 static void leja_dispatch_y(const FieldView& f, const Tiling& t, const LejaArgs& a, hipStream_t st) {
-  const bool nt = a.stream && !a.decide_only;
+  const bool nt = a.stream;
   if (a.first) {  // y_0 = v, FP64
     if (a.ystore_f32) leja_launch<TF, double, float, VEC, ADVF, true, false>(f, t, a, st);
     else leja_launch<TF, double, double, VEC, ADVF, true, false>(f, t, a, st);
@@ -1190,7 +1189,7 @@ static void leja_dispatch_y(const FieldView& f, const Tiling& t, const LejaArgs&
 hipError_t launch_leja_step(const FieldView& f, const Tiling& t, const LejaArgs& a, hipStream_t st) {
   // later terms read y_k in the storage type and never the augmented column
   if (!a.first && (a.w2 != nullptr || a.yin_f32 != a.ystore_f32 || a.k < 1)) return hipErrorInvalidValue;
-  if (!a.first && !a.decide_only && (a.pin == nullptr || a.pin == a.p)) return hipErrorInvalidValue;
+  if (!a.first && (a.pin == nullptr || a.pin == a.p)) return hipErrorInvalidValue;
   if (a.first && (a.yin_f32 || a.k != 0)) return hipErrorInvalidValue;
   ADL_DISPATCH_TILE(t, f, {
     if (f.f32) leja_dispatch_y<float, VEC, ADVF>(f, t, a, st);
@@ -1201,7 +1200,7 @@ hipError_t launch_leja_step(const FieldView& f, const Tiling& t, const LejaArgs&
 
 template <typename TF, typename TY, int VEC, bool ADVF, bool NT>
 static void leja2_launch(const FieldView& f, const Tiling& t, const LejaArgs& a, hipStream_t st) {
-  const dim3 grid(a.decide_only ? 1 : t.nblocks + 1), blk(kTileBlock2);
+  const dim3 grid(t.nblocks + 1), blk(kTileBlock2);
   const size_t lds = (size_t)kRing * kWave * VEC * sizeof(double);
   if (a.ev_start)
     hipExtLaunchKernelGGL((leja2_kernel<TF, TY, VEC, ADVF, NT>), grid, blk, lds, st, a.ev_start, a.ev_stop, 0, f, t,
@@ -1212,7 +1211,7 @@ static void leja2_launch(const FieldView& f, const Tiling& t, const LejaArgs& a,
 
 template <typename TF, typename TY, int VEC, bool ADVF, bool NT>
 static void leja2s_launch(const FieldView& f, const Tiling& t, const LejaArgs& a, hipStream_t st) {
-  const dim3 grid(a.decide_only ? 1 : t.nblocks + 1), blk(kTileBlock2);
+  const dim3 grid(t.nblocks + 1), blk(kTileBlock2);
   const size_t lds = staged_lds_bytes<VEC, ADVF>();
   if (a.ev_start)
     hipExtLaunchKernelGGL((leja2s_kernel<TF, TY, VEC, ADVF, NT>), grid, blk, lds, st, a.ev_start, a.ev_stop, 0, f,
@@ -1229,7 +1228,7 @@ static void leja2_any(const FieldView& f, const Tiling& t, const LejaArgs& a, hi
 
 template <bool LF, typename TF, typename TY, int VEC, bool ADVF>
 static void leja4_launch_lf(const FieldView& f, const Tiling& t, const LejaArgs& a, hipStream_t st) {
-  const dim3 grid(a.decide_only ? 1 : t.nblocks + 1), blk(kWave * kW4);
+  const dim3 grid(t.nblocks + 1), blk(kWave * kW4);
   const size_t lds = (2 * (size_t)kRing4 + (LF ? (size_t)kNF4<ADVF> * kQ4 : 0)) * kWave * VEC * sizeof(double);
   if (a.ev_start)
     hipExtLaunchKernelGGL((leja4_kernel<LF, TF, TY, VEC, ADVF>), grid, blk, lds, st, a.ev_start, a.ev_stop, 0, f, t,
@@ -1247,14 +1246,12 @@ hipError_t launch_leja4_step(const FieldView& f, const Tiling& t, const LejaArgs
   if (a.first || a.k < 1 || a.nterms != kT4 || a.w2 != nullptr || a.yin_f32 != a.ystore_f32 || a.stream)
     return hipErrorInvalidValue;
   if (t.rows != kR4 || t.bands != 1 || t.nblocks != t.ncb * t.nrb) return hipErrorInvalidValue;
-  if (!a.decide_only) {
-    // p_k is read while the stored p outputs (at least one) are written: all distinct
-    const double* o[5] = {a.pin, a.pmid, a.pmid2, a.pmid3, a.p};
-    if (a.pin == nullptr || (!a.pmid && !a.pmid2 && !a.pmid3 && !a.p)) return hipErrorInvalidValue;
-    for (int i = 1; i < 5; ++i)
-      for (int j = 0; j < i; ++j)
-        if (o[i] != nullptr && o[i] == o[j]) return hipErrorInvalidValue;
-  }
+  // p_k is read while the stored p outputs (at least one) are written: all distinct
+  const double* o[5] = {a.pin, a.pmid, a.pmid2, a.pmid3, a.p};
+  if (a.pin == nullptr || (!a.pmid && !a.pmid2 && !a.pmid3 && !a.p)) return hipErrorInvalidValue;
+  for (int i = 1; i < 5; ++i)
+    for (int j = 0; j < i; ++j)
+      if (o[i] != nullptr && o[i] == o[j]) return hipErrorInvalidValue;
   ADL_DISPATCH_TILE(t, f, {
     if (f.f32) {
       if (a.ystore_f32) leja4_launch<float, float, VEC, ADVF>(f, t, a, st);
@@ -1269,7 +1266,7 @@ hipError_t launch_leja4_step(const FieldView& f, const Tiling& t, const LejaArgs
 
 template <typename TF, typename TY, bool ADVF, bool NT, bool FIRST>
 static void leja3s_launch_k(const FieldView& f, const Tiling& t, const LejaArgs& a, hipStream_t st) {
-  const dim3 grid(a.decide_only ? 1 : t.nblocks + 1), blk(kTileBlock2);
+  const dim3 grid(t.nblocks + 1), blk(kTileBlock2);
   const size_t lds = staged3_lds_bytes<2, ADVF>();
   if (a.ev_start)
     hipExtLaunchKernelGGL((leja3s_kernel<TF, TY, ADVF, NT, FIRST>), grid, blk, lds, st, a.ev_start, a.ev_stop, 0, f,
@@ -1298,16 +1295,14 @@ static void leja3s_dispatch(const FieldView& f, const Tiling& t, const LejaArgs&
 hipError_t launch_leja3_step(const FieldView& f, const Tiling& t, const LejaArgs& a, hipStream_t st) {
   if (a.nterms != 3 || a.w2 != nullptr || a.yin_f32 != a.ystore_f32 || t.vec != 2) return hipErrorInvalidValue;
   // the first launch (terms 1 .. 3 from y_0 = v, FP64 Newton vectors only) or a later one
-  if (a.first ? (a.k != 0 || a.ystore_f32 || a.decide_only || a.pin != nullptr) : a.k < 1)
+  if (a.first ? (a.k != 0 || a.ystore_f32 || a.pin != nullptr) : a.k < 1)
     return hipErrorInvalidValue;
-  if (!a.decide_only) {
-    // p_k is read while the stored p outputs (at least one) are written: all distinct
-    const double* o[4] = {a.pin, a.pmid, a.pmid2, a.p};
-    if ((!a.first && a.pin == nullptr) || (!a.pmid && !a.pmid2 && !a.p)) return hipErrorInvalidValue;
-    for (int i = 1; i < 4; ++i)
-      for (int j = 0; j < i; ++j)
-        if (o[i] != nullptr && o[i] == o[j]) return hipErrorInvalidValue;
-  }
+  // p_k is read while the stored p outputs (at least one) are written: all distinct
+  const double* o[4] = {a.pin, a.pmid, a.pmid2, a.p};
+  if ((!a.first && a.pin == nullptr) || (!a.pmid && !a.pmid2 && !a.p)) return hipErrorInvalidValue;
+  for (int i = 1; i < 4; ++i)
+    for (int j = 0; j < i; ++j)
+      if (o[i] != nullptr && o[i] == o[j]) return hipErrorInvalidValue;
   if (a.stream) {
     if (f.f32) {
       if (a.ystore_f32) leja3s_dispatch<float, float, true>(f, t, a, st);
@@ -1330,7 +1325,7 @@ hipError_t launch_leja3_step(const FieldView& f, const Tiling& t, const LejaArgs
 
 template <typename TF, typename TY, bool ADVF, bool NT, bool STAGE>
 static void leja4s_launch_k(const FieldView& f, const Tiling& t, const LejaArgs& a, hipStream_t st) {
-  const dim3 grid(a.decide_only ? 1 : t.nblocks + 1), blk(kTileBlock2);
+  const dim3 grid(t.nblocks + 1), blk(kTileBlock2);
   const size_t lds = staged4_lds_bytes<2, ADVF>();
   if (a.ev_start)
     hipExtLaunchKernelGGL((leja4s_kernel<TF, TY, ADVF, NT, STAGE>), grid, blk, lds, st, a.ev_start, a.ev_stop, 0, f,
@@ -1361,17 +1356,15 @@ hipError_t launch_leja4s_step(const FieldView& f, const Tiling& t, const LejaArg
   // the sweep's first launch with its stage vector (terms 1 .. 3 from w = A u
   // + s, FP64 Newton vectors, no p input, not a decision launch), or four
   // later terms
-  if (a.stage ? (!a.first || a.k != 0 || a.nterms != 3 || a.ystore_f32 || a.decide_only || a.pin != nullptr)
+  if (a.stage ? (!a.first || a.k != 0 || a.nterms != 3 || a.ystore_f32 || a.pin != nullptr)
               : (a.first || a.k < 1 || a.nterms != 4))
     return hipErrorInvalidValue;
-  if (!a.decide_only) {
-    // p_k is read while the stored p outputs (at least one) are written: all distinct
-    const double* o[5] = {a.pin, a.pmid, a.pmid2, a.pmid3, a.p};
-    if ((!a.stage && a.pin == nullptr) || (!a.pmid && !a.pmid2 && !a.pmid3 && !a.p)) return hipErrorInvalidValue;
-    for (int i = 1; i < 5; ++i)
-      for (int j = 0; j < i; ++j)
-        if (o[i] != nullptr && o[i] == o[j]) return hipErrorInvalidValue;
-  }
+  // p_k is read while the stored p outputs (at least one) are written: all distinct
+  const double* o[5] = {a.pin, a.pmid, a.pmid2, a.pmid3, a.p};
+  if ((!a.stage && a.pin == nullptr) || (!a.pmid && !a.pmid2 && !a.pmid3 && !a.p)) return hipErrorInvalidValue;
+  for (int i = 1; i < 5; ++i)
+    for (int j = 0; j < i; ++j)
+      if (o[i] != nullptr && o[i] == o[j]) return hipErrorInvalidValue;
   if (a.stream) {
     if (f.f32) {
       if (a.ystore_f32) leja4s_dispatch<float, float, true>(f, t, a, st);
@@ -1395,7 +1388,7 @@ hipError_t launch_leja4s_step(const FieldView& f, const Tiling& t, const LejaArg
 hipError_t launch_leja2_step(const FieldView& f, const Tiling& t, const LejaArgs& a, hipStream_t st) {
   if (a.first || a.k < 1 || a.nterms != 2 || a.w2 != nullptr || a.yin_f32 != a.ystore_f32) return hipErrorInvalidValue;
   // p_k is read while the stored p outputs (at least one) are written: all distinct
-  if (!a.decide_only && (a.pin == nullptr || (a.p == nullptr && a.pmid == nullptr) || a.pin == a.p ||
+  if ((a.pin == nullptr || (a.p == nullptr && a.pmid == nullptr) || a.pin == a.p ||
                          a.pin == a.pmid || (a.p != nullptr && a.p == a.pmid)))
     return hipErrorInvalidValue;
   ADL_DISPATCH_TILE(t, f, {
