@@ -1577,6 +1577,7 @@ struct adl_batch {
   int gL = 0, gkprev = 0, gnprev = 0, gcovered = 0;
   // plan keys uploaded to d_plans
   std::vector<double> plan_alpha, plan_dt;
+  std::vector<int> plan_cap;  // the plan's degree cap: it has coefficients up to that term
   // graph
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
@@ -1981,7 +1982,9 @@ int upload_bins(adl_batch* B, double* const* u, const double* const* S, double d
     const double* Sb = S ? S[b] : nullptr;
     const int K = substeps_for(op->alpha, dt, op->rho_max);
     const bool active = op->has_bound && op->alpha < 0.0 && K == 1;
-    if (d.u != u[b] || d.S != Sb || d.dt != dt || d.tol != tol || d.active != (int)active) changed = true;
+    const int cap = std::min(op->max_degree, B->max_degree);
+    if (d.u != u[b] || d.S != Sb || d.dt != dt || d.tol != tol || d.active != (int)active || d.max_degree != cap)
+      changed = true;
     d.f = op->f;
     d.u = u[b];
     d.S = Sb;
@@ -2007,11 +2010,11 @@ int upload_bins(adl_batch* B, double* const* u, const double* const* S, double d
     d.pred[2] = op->tmp2;
     d.tol = tol;
     d.dt = dt;
-    d.max_degree = std::min(op->max_degree, B->max_degree);
+    d.max_degree = cap;
     d.active = active;
     d.d = B->d_plans + (size_t)b * 2 * M;
     d.shift = d.d + M;
-    if (active && (B->plan_alpha[b] != op->alpha || B->plan_dt[b] != dt)) {
+    if (active && (B->plan_alpha[b] != op->alpha || B->plan_dt[b] != dt || B->plan_cap[b] != cap)) {
       if (!plans_changed) BCHK(hipStreamSynchronize(st));
       Plan& P = get_plan(op, 1, op->alpha, dt);
       d.invg = P.invg;
@@ -2022,6 +2025,7 @@ int upload_bins(adl_batch* B, double* const* u, const double* const* S, double d
                      hipMemcpyHostToDevice));
       B->plan_alpha[b] = op->alpha;
       B->plan_dt[b] = dt;
+      B->plan_cap[b] = cap;
       B->order_key[b] = std::fabs(op->alpha) * dt;
       plans_changed = true;
     }
@@ -2301,6 +2305,7 @@ int adl_batch_create(int nbins, adl_op* const* ops, void* workspace, size_t ws_b
   B->order_key.assign(nbins, 0.0);
   B->plan_alpha.assign(nbins, NAN);
   B->plan_dt.assign(nbins, NAN);
+  B->plan_cap.assign(nbins, 0);
   build_tiles(B);
   hipError_t e = hipMemcpy(B->d_tile_bin, B->tile_bin.data(), sizeof(int) * B->total_tiles, hipMemcpyHostToDevice);
   if (e == hipSuccess)
