@@ -2143,7 +2143,8 @@ int enqueue_pipe_update(adl_batch* B, bool replayed, hipStream_t st) {
 // One step's pipeline sweep: the planned launches, u advanced where p is
 // stored, the outcomes read; bins still running go on (segments of a bin are
 // launched one after the other, so a bin's offset grows by the launches it sat
-// out), and bins that stopped between stored degrees are replayed.
+// out) up to the segment with their cap, and bins that stopped between stored
+// degrees are replayed.
 int pipe_step(adl_batch* B, hipStream_t st) {
   int rc = enqueue_pipe(B, 0, st);
   while (true) {
@@ -2157,8 +2158,12 @@ int pipe_step(adl_batch* B, hipStream_t st) {
     for (int b = 0; b < B->nbins; ++b) {
       BinDesc& d = B->bins[b];
       if (!d.active || B->h_ctl[b].stop) continue;
+      // (its cap lies in its last segment, whose decision then stopped it: a bin
+      // that has run that far and has not is left to the single-op path)
+      const int segs = std::min(seg_of(d.max_degree) + 1, d.segs + std::max(1, d.segs / 4));
+      if (segs <= d.segs) continue;
       d.off = B->pL - d.segs;
-      d.segs = std::min(seg_of(d.max_degree) + 1, d.segs + std::max(1, d.segs / 4));
+      d.segs = segs;
       run.push_back(b);
     }
     if (run.empty()) break;
