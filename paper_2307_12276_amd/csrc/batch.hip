@@ -2053,7 +2053,6 @@ int upload_bins(adl_batch* B, double* const* u, const double* const* S, double d
     B->pdirty = true;
   }
   if (pipe && pipe_plan(B, dt)) {
-    // (a replay of the step before may still read the maps)
     BCHK(hipStreamSynchronize(st));
     plans_changed = true;
     if (!B->pmap.empty())
@@ -2198,7 +2197,14 @@ int pipe_step(adl_batch* B, hipStream_t st) {
   if (first > 0) pipe_fields<true>(B, a, true, first, st);
   a.map = at + first;
   if ((int)map.size() > first) pipe_fields<true>(B, a, false, (int)map.size() - first, st);
-  return enqueue_pipe_update(B, true, st);
+  // (published and awaited like every other end of a step: the replays read
+  // tables that the next call may write, adl_batch_set_tile_rows for one, on
+  // another stream)
+  rc = enqueue_pipe_update(B, true, st);
+  if (rc == ADL_OK) rc = enqueue_publish(B, st);
+  if (rc != ADL_OK) return rc;
+  ++B->pubs;
+  return await_publication(B, B->pubs, st);
 }
 
 // Autotune results of this process, by tuning key.

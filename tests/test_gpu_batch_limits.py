@@ -113,3 +113,24 @@ def test_cap_lowered_between_steps():
             else:
                 op.midpoint_step(v, S, dt, 1e-10)
             assert rel(to_np(u), to_np(v)) <= 1e-13
+
+
+def test_tile_rows_set_right_after_steps_on_a_side_stream():
+    """Steps on a stream of the caller's, each with another dt (so that its
+    sweeps stop away from the expected degrees and are replayed), and the tile
+    tables written anew as soon as a step returns: a step has read them all by
+    then."""
+    import torch
+    ops, alone, us, vs, Ss, dt = bins([(512, 500), (256, 300), (384, 260), (128, 700)])
+    batch = A.Batch(ops, tile_rows=3)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for i, rows in enumerate((64, 1, 33, 2, 100, 5)):
+            got = batch.midpoint_step(us, Ss, dt * 0.8 ** i, 1e-10)
+            batch.set_tile_rows(rows)
+            for u, v, S, op, st in zip(us, vs, Ss, alone, got):
+                want = op.midpoint_step(v, S, dt * 0.8 ** i, 1e-10)
+                assert st["matvecs"] == want["matvecs"]
+                assert rel(to_np(u), to_np(v)) <= 1e-13
+                v.copy_(u)
