@@ -1377,7 +1377,8 @@ __device__ __forceinline__ void pipe_bin_decide(const PipeBatch& A, int b) {
     pn2 = pn[t];
     degree = k + t + 1;
     if (!isfinite(tn2) || !isfinite(pn2)) {
-      stop = 1; status = 2;
+      // (4: y^2 overflowed, d y need not have; the single-op path tells)
+      stop = 1; status = isfinite(pn2) ? 4 : 2;
     } else if (degree == 1 && m0 == 0.0) {
       stop = 1; status = 1; degree = 0;
     } else if (window_stop(hist, degree, sqrt(tn2), pn2, B.tol)) {
@@ -2568,7 +2569,8 @@ int adl_batch_midpoint_step(adl_batch* B, double* const* u, const double* const*
     }
   }
   // per-bin results; bins outside the kernel (substeps, zero operator) and
-  // bins that hit the degree cap take the single-op path (substeps allowed)
+  // bins that hit the degree cap or overflowed a norm take the single-op path
+  // (substeps allowed)
   int result = ADL_OK;
   for (int b = 0; b < B->nbins; ++b) {
     adl_op* op = B->ops[b];

@@ -270,7 +270,7 @@ static const Tiling& tiling_for(const adl_op* op, const void* a, const void* b =
 // --------------------------------------------------------------------------
 struct SweepOut {
   int degree = 0;
-  int status = 0;  // 1 converged, 2 non-finite, 3 degree cap
+  int status = 0;  // 1 converged, 2 non-finite, 3 degree cap (pipe_sweep: 4 a norm of y overflowed)
   bool anywhere = false;      // in: the result may be left in a workspace vector ...
   const double* p = nullptr;  // out: ... this one (else in the sweep's p_out)
   double* upd = nullptr;      // in: advance this vector by upd_h p, if that can be done without the host:
@@ -718,7 +718,18 @@ static int sweep(adl_op* op, Plan& P, const double* v, const double* w2, double 
   // stage_u (v null): the sweep of v = A stage_u + stage_s, whose first
   // launch computes that stage vector itself (stage_fusable)
   if (op->learned && op->budget > 0 && op->budget < maxdeg) maxdeg = op->budget;
-  if (pipe_ok(op)) return pipe_sweep(op, P, v, w2, w2scale, p_out, tol, maxdeg, st, out, stage_u, stage_s);
+  if (pipe_ok(op)) {
+    RETCHK(pipe_sweep(op, P, v, w2, w2scale, p_out, tol, maxdeg, st, out, stage_u, stage_s));
+    // (y grows by a factor a term where the interval leaves out part of the
+    // spectrum; the pipeline sums y^2, the kernels below (d y)^2, which may be
+    // finite still, so that the sweep goes on to its cap: substeps, no error)
+    if (out.status != 4) return ADL_OK;
+    if (stage_u) {
+      HIPCHK(launch_apply(op->f, tiling_for(op, stage_u, stage_s), stage_u, op->w1, stage_s, 1.0, nullptr, 0.0, st));
+      v = op->w1;
+      stage_u = stage_s = nullptr;
+    }
+  }
   // (the control block is cleared by block 0 of the first launch)
   const bool ys32 = op->storage == ADL_STORAGE_FP32_FIELDS_Y;
   const Tiling& T = tiling_for(op, stage_u ? stage_u : v, p_out);
@@ -957,6 +968,7 @@ static int sweep(adl_op* op, Plan& P, const double* v, const double* w2, double 
   }
   out.degree = op->host_ctl->degree;
   out.status = op->host_ctl->stop ? op->host_ctl->status : 3;
+  if (out.status == 4) out.status = 2;
   if (out.status == 1) {
     P.last_degree = out.degree;
     if (out.degree == 0) {
