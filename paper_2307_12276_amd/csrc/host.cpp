@@ -1435,7 +1435,9 @@ int adl_apply(adl_op* op, const double* x, double* y, void* stream) {
 // Power iteration on the pipeline kernel: kPipeMax applications a launch as
 // Newton terms without a shift, y_k = A y_{k-1} / s, whose norms give
 // lambda_k = s ||y_k|| / ||y_{k-1}||; s is the Gershgorin bound in the first
-// chunk and the last lambda after it, so that the norms stay in range.  A chunk
+// chunk and the last lambda after it, so that the norms stay in range as a rule
+// (else status 4: with strong advection at a node without diffusion to match,
+// the Gershgorin bound can be 1e5 times the vectors' growth).  A chunk
 // of launches ends with one block's tests of all its iterations, in order
 // (power_decide_kernel), and the host reads the outcome.  Four launches in the
 // first chunk, eight in the later ones: the method takes 20 - 60 iterations at
@@ -1494,6 +1496,39 @@ static int power_pipe(adl_op* op, double ag, int max_iter, double rtol, uint64_t
   }
 }
 
+// Power iteration with one application and normalisation a launch
+// (power_kernel), read by the host once per chunk.
+static int power_steps(adl_op* op, int max_iter, double rtol, uint64_t seed, hipStream_t st) {
+  HIPCHK(launch_ctl_reset(op->ctl, 1, st));
+  const Tiling& T = op->t;
+  HIPCHK(launch_power_init(T, op->n, seed, op->tmp, op->partials, st));
+  double* bufs[2] = {op->tmp, op->tmp2};
+  PowerArgs pa{};
+  pa.rtol = rtol;
+  pa.max_iter = max_iter;
+  pa.nb = T.nblocks;
+  pa.partials = op->partials;
+  pa.ctl = op->ctl;
+  int launched = 0;
+  while (true) {
+    const int chunk = std::min(max_iter - launched, launched == 0 ? 64 : 128);
+    for (int i = 0; i < chunk; ++i) {
+      const int k = launched + i;
+      pa.x = bufs[k & 1];
+      pa.w = bufs[(k + 1) & 1];
+      pa.k = k;
+      pa.decide_only = 0;
+      HIPCHK(launch_power_step(op->f, T, pa, st));
+    }
+    launched += chunk;
+    pa.k = launched;
+    pa.decide_only = 1;
+    HIPCHK(launch_power_step(op->f, T, pa, st));
+    RETCHK(read_ctl(op, st));
+    if (op->host_ctl->stop || launched >= max_iter) return ADL_OK;
+  }
+}
+
 int adl_spectral_bound(adl_op* op, int method, int max_iter, double rtol, uint64_t seed, double* alpha_out,
                        int* iters_out, void* stream) {
   RETCHK(check_op(op));
@@ -1507,38 +1542,11 @@ int adl_spectral_bound(adl_op* op, int method, int max_iter, double rtol, uint64
   if (method == ADL_BOUND_POWER) {
     if (max_iter < 1) return fail(ADL_EINVAL, "max_iter must be >= 1");
     if (!(rtol > 0.0)) return fail(ADL_EINVAL, "rtol must be > 0");
-    if ((long)op->nx * op->ny < kPipePoints) {
-      RETCHK(power_pipe(op, ag, max_iter, rtol, seed, st));
-    } else {
-      HIPCHK(launch_ctl_reset(op->ctl, 1, st));
-      const Tiling& T = op->t;
-      HIPCHK(launch_power_init(T, op->n, seed, op->tmp, op->partials, st));
-      double* bufs[2] = {op->tmp, op->tmp2};
-      PowerArgs pa{};
-      pa.rtol = rtol;
-      pa.max_iter = max_iter;
-      pa.nb = T.nblocks;
-      pa.partials = op->partials;
-      pa.ctl = op->ctl;
-      int launched = 0;
-      while (true) {
-        const int chunk = std::min(max_iter - launched, launched == 0 ? 64 : 128);
-        for (int i = 0; i < chunk; ++i) {
-          const int k = launched + i;
-          pa.x = bufs[k & 1];
-          pa.w = bufs[(k + 1) & 1];
-          pa.k = k;
-          pa.decide_only = 0;
-          HIPCHK(launch_power_step(op->f, T, pa, st));
-        }
-        launched += chunk;
-        pa.k = launched;
-        pa.decide_only = 1;
-        HIPCHK(launch_power_step(op->f, T, pa, st));
-        RETCHK(read_ctl(op, st));
-        if (op->host_ctl->stop || launched >= max_iter) break;
-      }
-    }
+    const bool pipe = (long)op->nx * op->ny < kPipePoints;
+    if (pipe) RETCHK(power_pipe(op, ag, max_iter, rtol, seed, st));
+    // (again where its vectors left the range, or if lambda = 0: a vector
+    // normalised at every iteration)
+    if (!pipe || op->host_ctl->status == 4) RETCHK(power_steps(op, max_iter, rtol, seed, st));
     const Ctl& c = *op->host_ctl;
     if (c.status == 2) return fail(ADL_ENAN, "non-finite value in power iteration");
     iters = c.iters;

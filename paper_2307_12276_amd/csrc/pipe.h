@@ -91,6 +91,7 @@ hipError_t launch_pipe_update(const PipeUpdate& a, hipStream_t st);
 // chunk (kPipeMax iterations, the last one maybe fewer) left its partials at
 // partials + 3 kPipeMax nb i, ||y_0||^2 of the first chunk is the sum of
 // init[0 .. ninit) (else ctl->tn2).  lambda_j = scale ||y_j|| / ||y_{j-1}||.
+// Status 4: a norm out of range.
 struct PowerDecide {
   const double* partials;
   const double* init;

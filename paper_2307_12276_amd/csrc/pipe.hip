@@ -99,8 +99,10 @@ hipError_t launch_pipe_update(const PipeUpdate& a, hipStream_t st) {
 }
 
 // One wave per iteration's sum, then the tests in order: iteration j stops the
-// method where lambda_j is not finite, is zero, or differs from lambda_{j-1} (0
-// before the first) by at most rtol lambda_j.
+// method where lambda_j differs from lambda_{j-1} (0 before the first) by at most
+// rtol lambda_j, and (status 4) where lambda_j or the norm it is taken from is
+// zero, not finite or so far from 1 that sums of squares lose digits.
+constexpr double kPowerLow = 1e-150, kPowerHigh = 1e150, kPowerLow2 = 1e-200, kPowerHigh2 = 1e200;
 constexpr int kPowerIters = 8 * kPipeMax;  // most iterations of a chunk
 __global__ __launch_bounds__(16 * kWave) void power_decide_kernel(PowerDecide A) {
   __shared__ double n2[kPowerIters + 1];
@@ -125,10 +127,8 @@ __global__ __launch_bounds__(16 * kWave) void power_decide_kernel(PowerDecide A)
     ++k;
     lam_prev = lam;
     lam = n2[j] == 0.0 ? 0.0 : A.scale * sqrt(n2[j] / n2[j - 1]);
-    if (!isfinite(lam)) {
-      stop = 1; status = 2;
-    } else if (lam == 0.0) {
-      stop = 1; status = 1;
+    if (!(lam > kPowerLow && lam < kPowerHigh && n2[j] > kPowerLow2 && n2[j] < kPowerHigh2)) {
+      stop = 1; status = 4;
     } else if (fabs(lam - lam_prev) <= A.rtol * lam) {
       stop = 1; status = 1;
     } else if (k >= A.max_iter) {
