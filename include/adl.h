@@ -170,7 +170,8 @@ int adl_op_set_tiling(adl_op* op, int rows, int cols_per_lane);
  * whose two-term tiling has two columns per lane (ADL_EINVAL otherwise);
  * mode = 6 computes four terms per launch with the input rows staged in LDS
  * (y_{k+1} .. y_{k+3} kept in LDS; nx even and at least 128, ADL_EINVAL
- * otherwise); mode = 0 launches one kernel per term.
+ * otherwise); mode = 0 launches one kernel per term, and per application
+ * of a power iteration (the other modes seven per launch, below 2^28 points).
  * A fused launch stores y and p of its last term only (mode 1: also p of the
  * degree the plan last took); when the sweep stops at another term of a launch, the launch is run again on its inputs to
  * store p of that term (the same arithmetic, so the same values).  Results

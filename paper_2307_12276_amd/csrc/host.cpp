@@ -1542,7 +1542,8 @@ int adl_spectral_bound(adl_op* op, int method, int max_iter, double rtol, uint64
   if (method == ADL_BOUND_POWER) {
     if (max_iter < 1) return fail(ADL_EINVAL, "max_iter must be >= 1");
     if (!(rtol > 0.0)) return fail(ADL_EINVAL, "rtol must be > 0");
-    const bool pipe = (long)op->nx * op->ny < kPipePoints;
+    // (mode 0: one application per launch, like its sweeps)
+    const bool pipe = op->fuse_terms != 0 && (long)op->nx * op->ny < kPipePoints;
     if (pipe) RETCHK(power_pipe(op, ag, max_iter, rtol, seed, st));
     // (again where its vectors left the range, or if lambda = 0: a vector
     // normalised at every iteration)
