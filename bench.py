@@ -133,6 +133,24 @@ def kernel_roofline(op_ms, launches, nbytes):
     return avg_ms, per_launch, achieved
 
 
+def read_launches(op):
+    """(ms, launches, bytes, terms, {"first": ..., "later": ...}) of the profiled
+    Newton-Leja launches, each counted as the one launch it is: the library's
+    kinds hold launches of up to four terms, and book one of more as groups of
+    three and a remainder."""
+    import paper_2307_12276_amd as A
+    first = op.profile_read_kind(A.LAUNCH_FIRST)
+    rest = [op.profile_read_kind(k) for k in (A.LAUNCH_ONE, A.LAUNCH_TWO, A.LAUNCH_THREE, A.LAUNCH_FOUR)]
+    ms, launches, nbytes = op.profile_read()
+    terms = first[3] + sum(r[3] for r in rest)
+
+    def kind(ms, n, terms):
+        return {"launches": n, "avg_us": 1e3 * ms / n if n else None, "terms": terms}
+
+    return ms, launches, nbytes, terms, {"first": kind(first[0], first[1], first[3]),
+                                         "later": kind(ms - first[0], launches - first[1], terms - first[3])}
+
+
 PIPE_KERNEL = ("pipe_kernel (up to seven Newton terms per launch as a pipeline of waves, the first launch with the "
                "stage vector, non-temporal hints on the vectors read or written once)")
 
@@ -660,13 +678,10 @@ def headline(args):
         op.midpoint_step(u, S[n], w.dt, w.tol)
     torch.cuda.synchronize()
     el_prof = time.perf_counter() - t1
-    kinds = {k: op.profile_read_kind(getattr(A, "LAUNCH_" + k.upper()))
-             for k in ("first", "one", "two", "three", "four")}
     # every Newton-Leja launch: its time, and the bytes a launch cannot do
     # without (one pass over memory for all of its terms)
-    ms2, n2, fused2 = op.profile_read()
+    ms2, n2, fused2, terms2, kinds = read_launches(op)
     op.profile(False)
-    terms2 = sum(k[3] for k in kinds.values())
     avg_s = ms2 / max(n2, 1) * 1e-3
     alg = fused2 / max(n2, 1)
     achieved = alg / avg_s / 1e9 if n2 else 0.0
@@ -694,13 +709,11 @@ def headline(args):
                                                            % (terms2 / max(n2, 1)),
                      "avg_kernel_us": avg_s * 1e6, "launches": n2,
                      "terms_per_launch": terms2 / max(n2, 1),
-                     "timing": "HIP events on each Newton-Leja dispatch, second pass of %d steps (%.3fs); in "
-                               "launch_kinds a launch of more than three terms counts as groups of three and a "
-                               "remainder" % (args.steps, el_prof),
+                     "timing": "HIP events on each Newton-Leja dispatch, second pass of %d steps (%.3fs)"
+                               % (args.steps, el_prof),
                      "traffic_source": "profiles/%s (rocprofv3 FETCH_SIZE and WRITE_SIZE per dispatch, "
                                        "scaled by a 1 GiB copy), bytes per launch" % os.path.basename(TRAFFIC_FILE)},
-        "launch_kinds": {k: {"launches": v[1], "avg_us": 1e3 * v[0] / v[1] if v[1] else None, "terms": v[3]}
-                         for k, v in kinds.items()},
+        "launch_kinds": kinds,
     }
     if traffic:
         out["roofline"]["traffic_GBs"] = traffic / avg_s / 1e9

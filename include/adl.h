@@ -135,9 +135,13 @@ int adl_op_profile_read(adl_op* op, double* kernel_ms, long long* launches, doub
 
 /* The same counters split by launch kind (read before adl_op_profile_read,
  * which resets them): ADL_LAUNCH_FIRST = the first term of a sweep (y_0 = v,
- * the augmented column), ADL_LAUNCH_ONE / _TWO / _THREE / _FOUR = launches of
- * one, two, three or four later terms.  terms (may be NULL) = Newton terms
- * those launches computed.  ADL_EINVAL for another kind. */
+ * the augmented column, and with modes 1, 5 and 6 of the term fusion maybe
+ * further terms), ADL_LAUNCH_ONE / _TWO / _THREE / _FOUR = launches of
+ * one, two, three or four later terms.  A later launch of mode 1, of up to
+ * seven terms, is booked as groups of three terms and a remainder, its time and
+ * bytes shared out over its terms, so these counts are no launches;
+ * adl_op_profile_read counts each launch once.  terms (may be NULL) = Newton
+ * terms those launches computed.  ADL_EINVAL for another kind. */
 enum { ADL_LAUNCH_FIRST = 0, ADL_LAUNCH_ONE = 1, ADL_LAUNCH_TWO = 2, ADL_LAUNCH_FOUR = 3, ADL_LAUNCH_THREE = 4 };
 int adl_op_profile_read_kind(const adl_op* op, int kind, double* kernel_ms, long long* launches,
                              double* bytes, long long* terms);

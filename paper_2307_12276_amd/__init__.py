@@ -302,8 +302,10 @@ class Op:
 
     def profile_read_kind(self, kind: int):
         """(kernel ms, launches, algorithmic bytes, Newton terms) of the timed
-        Leja launches of one kind (LAUNCH_FIRST / _ONE / _TWO / _THREE / _FOUR); call
-        before profile_read, which resets the counters."""
+        Leja launches of one kind (LAUNCH_FIRST / _ONE / _TWO / _THREE / _FOUR; a
+        later launch of mode 1 is booked as groups of three terms and a
+        remainder); call before profile_read, which counts each launch once
+        and resets the counters."""
         ms = ctypes.c_double()
         n = ctypes.c_longlong()
         b = ctypes.c_double()
