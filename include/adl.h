@@ -309,6 +309,8 @@ int adl_batch_get_tile_rows(const adl_batch* b, int* rows);
  * registers); mode = 0 launches one kernel per term.  ADL_EINVAL for other
  * values, and for mode 3 when a bin is narrower or odd. */
 int adl_batch_set_term_fusion(adl_batch* batch, int mode);
+/* Back to the steps of a batch without a mode set. */
+int adl_batch_reset_term_fusion(adl_batch* batch);
 
 /* Autotuner: times the launches of one step (stage and sweep; u is not
  * modified) for each of the ncand candidate tile heights (host array) and

@@ -120,6 +120,7 @@ _SIG = {
     "adl_batch_set_tile_rows": (_I, [_P, _I]),
     "adl_batch_get_tile_rows": (_I, [_P, ctypes.POINTER(_I)]),
     "adl_batch_set_term_fusion": (_I, [_P, _I]),
+    "adl_batch_reset_term_fusion": (_I, [_P]),
     "adl_batch_autotune": (_I, [_P, ctypes.POINTER(_P), ctypes.POINTER(_P), _D, _D, ctypes.POINTER(_I), _I,
                                 ctypes.POINTER(_I), ctypes.POINTER(_D), _P]),
     "adl_batch_midpoint_step": (_I, [_P, ctypes.POINTER(_P), ctypes.POINTER(_P), _D, _D, _I,
@@ -465,9 +466,13 @@ class Batch:
         (a graph step's default when every bin has nx even and >= 128), True/1
         two after a launch of the first term alone (its default otherwise),
         False/0 one.  Until a mode is set, eager steps run up to seven terms
-        per launch on the pipeline kernel."""
+        per launch on the pipeline kernel (again after reset_term_fusion)."""
         m = int(mode) if not isinstance(mode, bool) else int(mode)
         _check(lib().adl_batch_set_term_fusion(self.handle, m))
+
+    def reset_term_fusion(self):
+        """Back to the steps of a batch without a mode set."""
+        _check(lib().adl_batch_reset_term_fusion(self.handle))
 
     def autotune(self, us, S_halfs, dt: float, tol: float, candidates=(8, 16, 32), stream=None):
         up, sp = self._ptr_arrays(us, S_halfs)

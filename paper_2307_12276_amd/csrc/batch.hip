@@ -2294,8 +2294,8 @@ int adl_batch_create(int nbins, adl_op* const* ops, void* workspace, size_t ws_b
   B->ops.assign(ops, ops + nbins);
   B->nbins = nbins;
   B->vec = all_even ? 2 : 1;
-  // three terms per launch by default where every bin allows them (C4, 256
-  // bins: 3.63-3.67 ms per step with two terms per launch, 2.94-3.02 with three)
+  // graph steps: three terms per launch where every bin allows them (256 bins:
+  // 3.63-3.67 ms per step with two terms per launch, 2.94-3.02 with three)
   B->three = all_even ? 1 : 0;
   B->f32 = f32;
   B->advf = advf;
@@ -2378,13 +2378,9 @@ int adl_batch_set_tile_rows(adl_batch* B, int rows) {
   return ADL_OK;
 }
 
-int adl_batch_set_term_fusion(adl_batch* B, int mode) {
-  if (!B || (mode != 0 && mode != 1 && mode != 3)) return bfail(ADL_EINVAL, "term fusion mode must be 0, 1 or 3");
-  if (mode == 3 && B->vec != 2)
-    return bfail(ADL_EINVAL, "three terms per launch need every bin at two columns per lane (nx even, >= 128)");
-  const int two = mode != 0, three = mode == 3;
-  if (two == B->two && three == B->three && !B->pipe) return ADL_OK;
-  B->pipe = 0;
+static int set_terms(adl_batch* B, int pipe, int two, int three) {
+  if (pipe == B->pipe && two == B->two && three == B->three) return ADL_OK;
+  B->pipe = pipe;
   B->two = two;
   B->three = three;
   BCHK(hipStreamSynchronize(B->cap_stream));
@@ -2397,6 +2393,18 @@ int adl_batch_set_term_fusion(adl_batch* B, int mode) {
     B->graph = nullptr;
   }
   return ADL_OK;
+}
+
+int adl_batch_set_term_fusion(adl_batch* B, int mode) {
+  if (!B || (mode != 0 && mode != 1 && mode != 3)) return bfail(ADL_EINVAL, "term fusion mode must be 0, 1 or 3");
+  if (mode == 3 && B->vec != 2)
+    return bfail(ADL_EINVAL, "three terms per launch need every bin at two columns per lane (nx even, >= 128)");
+  return set_terms(B, 0, mode != 0, mode == 3);
+}
+
+int adl_batch_reset_term_fusion(adl_batch* B) {
+  if (!B) return bfail(ADL_EINVAL, "null batch");
+  return set_terms(B, 1, 1, B->vec == 2);
 }
 
 int adl_batch_get_tile_rows(const adl_batch* B, int* rows) {

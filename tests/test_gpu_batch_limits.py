@@ -134,3 +134,25 @@ def test_tile_rows_set_right_after_steps_on_a_side_stream():
                 assert st["matvecs"] == want["matvecs"]
                 assert rel(to_np(u), to_np(v)) <= 1e-13
                 v.copy_(u)
+
+
+@pytest.mark.parametrize("shapes", [[(128, 64), (256, 40)], [(113, 33), (64, 50)]])
+def test_mode_set_and_reset(shapes):
+    """Modes of the term fusion between steps of one batch, eager and as a graph,
+    and back to the default: bitwise the pipeline's steps then."""
+    ops, alone, us, vs, Ss, dt = bins(shapes)
+    batch, plain = A.Batch(ops), A.Batch(alone)
+    for mode in (None, False, None, 3 if shapes[0][0] == 128 else True, None):
+        if mode is None:
+            batch.reset_term_fusion()
+        else:
+            batch.set_term_fusion(mode)
+        for use_graph in (False, True, False):
+            batch.midpoint_step(us, Ss, dt, 1e-10, use_graph=use_graph)
+            plain.midpoint_step(vs, Ss, dt, 1e-10)
+            for u, v in zip(us, vs):
+                a, b = to_np(u), to_np(v)
+                if mode is None and not use_graph:
+                    assert np.array_equal(a, b)
+                assert rel(a, b) <= 1e-12
+                u.copy_(v)
