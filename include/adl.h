@@ -149,9 +149,11 @@ int adl_op_profile_read_kind(const adl_op* op, int kind, double* kernel_ms, long
 /* Tiling of the stencil kernels (the autotuner's knobs): rows = rows each
  * wave computes per tile (a block of four waves covers 4 * rows rows of one
  * strip; default 1), cols_per_lane = columns per lane (1, or 2 for even
- * nx >= 128); 0 selects the built-in default for each.  adl_op_get_tiling
- * reports the tiling in use and the worker block count of a launch (any
- * output pointer may be NULL). */
+ * nx >= 128); 0 selects the built-in default for each.  Applications and the
+ * sweeps of modes 0 and 2 .. 6 use it; mode 1's sweeps and power iterations
+ * below 2^28 points choose their own.  adl_op_get_tiling reports the tiling
+ * and the worker block count of an application (any output pointer may be
+ * NULL). */
 int adl_op_set_tiling(adl_op* op, int rows, int cols_per_lane);
 
 /* Newton terms per launch of a sweep (Sec. 2 recurrence): mode = 1 (the
@@ -159,8 +161,9 @@ int adl_op_set_tiling(adl_op* op, int rows, int cols_per_lane);
  * as a pipeline of waves along the rows (y_{k+1} .. y_{k+6} and the p between
  * handed on through LDS; read y_k, the fields and p_k once, write y_{k+7} and
  * p_{k+7}), or on small grids (up to about 320^2) on tiles held in registers
- * with a frame of seven points; a midpoint step without substeps forms its stage vector A u + S in
- * the first launch.  On grids of 2^28 points and more it computes three (mode
+ * with a frame of seven points; a midpoint step without substeps forms its
+ * stage vector A u + S in the first launch.  On grids of 2^28 points and more,
+ * and in a sweep whose squared norms overflow there, it computes three (mode
  * 5's form; with FP64 Newton vectors and no augmented column among terms
  * 1 .. 3 the first launch takes three terms too and forms the stage vector),
  * or where that does not apply two in mode 2's form;
@@ -177,8 +180,9 @@ int adl_op_set_tiling(adl_op* op, int rows, int cols_per_lane);
  * otherwise); mode = 0 launches one kernel per term, and per application
  * of a power iteration (the other modes seven per launch, below 2^28 points).
  * A fused launch stores y and p of its last term only (mode 1: also p of the
- * degree the plan last took); when the sweep stops at another term of a launch, the launch is run again on its inputs to
- * store p of that term (the same arithmetic, so the same values).  Results
+ * last two degrees the plan took); when the sweep stops at another term of a
+ * launch, the launch is run again on its inputs to store p of that term (the
+ * same arithmetic, so the same values).  Results
  * agree to rounding (the block partial sums of the norms are grouped
  * differently).  ADL_EINVAL for other values. */
 int adl_op_set_term_fusion(adl_op* op, int mode);
@@ -270,10 +274,9 @@ int adl_exp_quad2_step(adl_op* op, double* u, const double* S1, const double* S2
 
 /* ------------------------------------------------------------------------
  * Batched momentum bins: independent operators (different grids, different
- * intervals) advanced together.  Each kernel of a step covers the tiles of
- * all bins (stage, one launch per Leja term, final decision); the step's
- * launches are captured once in a hipGraph and replayed, one graph launch
- * per step.  Bins needing substeps, a zero operator or more terms than the
+ * intervals) advanced together.  Each launch of a step covers the blocks or
+ * tiles of all bins still running; with use_graph the step's launches are
+ * captured once in a hipGraph and replayed.  Bins needing substeps, a zero operator or more terms than the
  * batch allows are advanced by the single-op path inside the same call.
  * ---------------------------------------------------------------------- */
 

@@ -507,10 +507,12 @@ static bool stage_fusable(const adl_op* op, const double* u, const double* s, do
 //
 // Chunks: the first one covers the plan's last degree (the first sweep of a
 // plan: a guess from rho h) in whole launches.  p is also stored at the plan's
-// last degree and at the one before it, where they are not a launch's last
-// term (8 B per point more on one launch each; a sequence of steps alternates
-// between neighbouring degrees as a rule), so that a sweep stopping there needs
-// no replay (175 us at 4096^2) and one stopping a little later no further chunk.
+// last degree and at the last one that differed from it, where they are not a
+// launch's last term (8 B per point more on one launch each), so that a sweep
+// stopping there needs no replay (175 us at 4096^2).  Of 200 steps at 64^2, 512^2
+// and 1024^2, 100 at 2048^2 and 60 at 4096^2, 92 - 99 % took the last degree, up
+// to 4 % the one before, and up to 5 % (a degree that falls from step to step)
+// were replayed; none needed a second chunk.
 static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, double w2scale, double* p_out,
                       double tol, int maxdeg, hipStream_t st, SweepOut& out, const double* stage_u,
                       const double* stage_s) {

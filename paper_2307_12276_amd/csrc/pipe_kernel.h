@@ -11,10 +11,11 @@
 // FP64) then covers nst terms; a row of 128 points costs a wave 44 FP64 and 8
 // shift instructions.
 //
-// What bounds it: at 4096^2 a launch of seven terms takes 206 us (950 MB; a copy
-// of that size 180 us) where the three-term staged kernel took 183 us for
-// three; the rest is LDS traffic, 7 KB a row and stage (coefficients, y, p), and
-// issue, two blocks of eight waves a CU.  Up to 1024^2 the latency of rows + 21
+// What bounds it: at 4096^2 a launch of seven terms takes 206 - 225 us by HIP
+// events (939.5 MB needed, 1010 MB moved by the counters: 193 us at the rate of
+// a copy) where the three-term staged kernel took 183 us for three; the rest is
+// LDS traffic, 7 KB a row and stage (coefficients, y, p), and issue, two blocks of
+// eight waves a CU.  Up to 1024^2 the latency of rows + 21
 // ticks of 0.35 - 0.45 us bounds it (512^2: 16 us a launch of seven terms, where
 // four terms in LDS took 15.4).  Two rows a tick or two stages a wave gain 7 % at
 // 4096^2 but lose 20 - 80 % up to 1024^2 (longer ticks); 3 rows in flight a wave

@@ -444,8 +444,8 @@ __global__ __launch_bounds__(kTileBlock2) void leja2_kernel(FieldView F, Tiling 
 }
 
 // ---------------------------------------------------------------------------
-// Four Newton-Leja terms per launch (k >= 1), for grids of up to 2^20 points:
-// there a two-term launch is mostly fixed cost (measured on MI355X, FP64:
+// Four Newton-Leja terms per launch (k >= 1; mode 4), for grids of up to 2^20
+// points: there a two-term launch is mostly fixed cost (measured on MI355X, FP64:
 // 5.8 us at 256^2, 8.5 us at 512^2, 16 us at 768^2), which four terms share
 // out twice as far.  A block owns kR4 output rows of a strip of 56*VEC
 // output columns (lanes 4..59 of a wave strip that starts 4*VEC columns to
