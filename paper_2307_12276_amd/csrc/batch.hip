@@ -1377,8 +1377,7 @@ __device__ __forceinline__ void pipe_bin_decide(const PipeBatch& A, int b) {
     pn2 = pn[t];
     degree = k + t + 1;
     if (!isfinite(tn2) || !isfinite(pn2)) {
-      // (4: y^2 overflowed, d y need not have; the single-op path tells)
-      stop = 1; status = isfinite(pn2) ? 4 : 2;
+      stop = 1; status = 2;
     } else if (degree == 1 && m0 == 0.0) {
       stop = 1; status = 1; degree = 0;
     } else if (window_stop(hist, degree, sqrt(tn2), pn2, B.tol)) {
@@ -2600,9 +2599,11 @@ int adl_batch_midpoint_step(adl_batch* B, double* const* u, const double* const*
         s.max_degree = s.last_degree = c.degree;
         s.substeps = 1;
         s.alpha = op->alpha;
-      } else if (c.status == 2) {
+      } else if (c.status == 2 && !(pipe && std::isfinite(c.pn2))) {
         code = ADL_ENAN;
       } else {
+        // (the cap; or the pipeline's tn2 = d^2 sum y^2 overflowed where p did
+        // not: d y need not have)
         single = true;
       }
     }

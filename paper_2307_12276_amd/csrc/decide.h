@@ -116,8 +116,7 @@ __device__ __forceinline__ void leja_decide(const Args& A, double* dsh = nullptr
     double m0 = 0.0;
     for (int s = 0; s < segs; ++s) m0 = nanmax(m0, sh[2 * nt * segs + s]);
     if (!isfinite(tn2) || !isfinite(pn2)) {
-      // (p finite: y is, and its square overflowed; d y need not have)
-      stop = 1; status = isfinite(pn2) ? 4 : 2; degree = deg;
+      stop = 1; status = 2; degree = deg;
     } else if (deg == 1 && m0 == 0.0) {
       stop = 1; status = 1; degree = 0;
     } else if (window_stop(hist, deg, sqrt(tn2), pn2, A.tol)) {

@@ -681,6 +681,12 @@ static int pipe_sweep(adl_op* op, Plan& P, const double* v, const double* w2, do
   }
   out.degree = op->host_ctl->degree;
   out.status = op->host_ctl->stop ? op->host_ctl->status : 3;
+  if (out.status == 2) {
+    // (p finite: y is too, and the square that overflowed was y's; d y need not
+    // have)
+    RETCHK(read_ctl(op, st));
+    if (std::isfinite(op->host_ctl->pn2)) out.status = 4;
+  }
   if (out.status != 1) return ADL_OK;
   const int m = out.degree;
   if (m != P.last_degree) P.prev_degree = P.last_degree;
@@ -970,7 +976,6 @@ static int sweep(adl_op* op, Plan& P, const double* v, const double* w2, double 
   }
   out.degree = op->host_ctl->degree;
   out.status = op->host_ctl->stop ? op->host_ctl->status : 3;
-  if (out.status == 4) out.status = 2;
   if (out.status == 1) {
     P.last_degree = out.degree;
     if (out.degree == 0) {

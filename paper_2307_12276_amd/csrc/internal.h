@@ -73,7 +73,7 @@ __device__ __forceinline__ bool window_stop(double (&hist)[kStopHist], int m, do
 // of a launch (fixed-order reduction), read by the next launch and the host.
 struct Ctl {
   int stop;             // 1: every later launch of this sweep returns at once
-  int status;           // 0 running, 1 converged, 2 non-finite, 3 degree cap, 4 a norm out of range
+  int status;           // 0 running, 1 converged, 2 non-finite, 3 degree cap, 4 (power iteration) a norm out of range
   int degree;           // Newton terms (matrix applications) so far
   unsigned int ticket;  // arrival counter of the running launch (reset by last block)
   double tn2, pn2;      // ||d y||^2, ||p||^2 of the last term

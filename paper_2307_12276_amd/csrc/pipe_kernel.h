@@ -519,7 +519,7 @@ __device__ __forceinline__ void pipe_stage(const FieldView& F, const Args& A, do
       // norms (on every lane of the strip; the frame's are dropped at the end)
       // and stores of the run's own rows.  (y^2 is summed and scaled by d^2 once:
       // a product d y per point made every pipeline case 2 % slower, 4096^2
-      // steps 5353 -> 5461 us.  Where y^2 overflows, the decision says so.)
+      // steps 5353 -> 5461 us.  The host sees to a y^2 that overflows.)
 #pragma unroll
       for (int v = 0; v < 2; ++v) {
         yn2[v] = __builtin_fma(y[v], y[v], yn2[v]);
